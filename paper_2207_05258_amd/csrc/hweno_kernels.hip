@@ -280,6 +280,13 @@ __device__ __forceinline__ bool obstacle_near(const EdgeArgs& e, int c0, int c1,
   return e.oj > 0 && c1 > e.oi && r0 < e.oj && r1 > 0;
 }
 
+// Field f as the stage tile holds it: derivatives times their cell size (the
+// differences and linear forms of the scheme are in these units).
+template <typename T>
+__device__ __forceinline__ T staged(T x, int f, int m, T dx, T dy) {
+  return f < m ? x : x * (f < 2 * m ? dx : dy);
+}
+
 // Solid cells of the staged tile take the mirror image of the fluid across the
 // obstacle's front face (d = 0) or top face (d = 1), with the wall signs of
 // that direction, read from the stage input.  Cells deeper than two inside the
@@ -300,31 +307,29 @@ __device__ __forceinline__ void obstacle_mirror(const StageArgs<T>& a, const Edg
     const long long g = (long long)sj * nx + si;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-      const T x = gld(a.in + f * a.fs + g);
+      const T x = staged(gld(a.in + f * a.fs + g), f, M, T(a.dx), T(a.dy));
       sm[f * HR * W + q] = mirror_sign(f, M, true, d) < 0 ? -x : x;
     }
   }
 }
-
-// Where the stage kernels sum the linear derivative fluxes of an x-interface
-// over its four stencil points: in registers in FP64 (two waves per SIMD leave
-// room; the sums of the y-interfaces stay in LDS, as the x results held there
-// leave none), in their flux-buffer slots in FP32 (at five waves per SIMD the
-// registers spill 136-144 B per lane).
-template <typename T>
-struct LinReg {
-  static constexpr bool value = sizeof(T) == 8;
-};
 
 // ---------------------------------------------------------------------------
 // One tile of one stage (K = 1, 2, 3) or of the right-hand side (K = 0).
 // NT threads; TX x TY cells (TX*TY <= NT); sm, fb: LDS staging buffers.
 // Returns this thread's contribution to the next stage's speeds.
 // ---------------------------------------------------------------------------
-// CL: the characteristic variant of the limiter (Euler; a separate
-// instantiation so the default kernels carry none of its code).
+// MODE: which fields the reconstruction and the limiter of the Euler equations
+// work on, separate instantiations because a branch between them costs the
+// default kernels their registers (FP64: 250 instead of 218 VGPRs).  The scalar
+// laws use MODE_COMP.
 // EDG: edge-described sides (2D Euler; a separate instantiation), read from *e.
-template <typename T, int PHYS, int DIM, int K, int TX, int TY, int NT, bool CL, bool EDG = false>
+enum {
+  MODE_CHAR = 0,       // characteristic reconstruction, limiter component by component
+  MODE_CHAR_LIM = 1,   // characteristic reconstruction and limiter
+  MODE_COMP = 2        // reconstruction component by component, either limiter
+};
+
+template <typename T, int PHYS, int DIM, int K, int TX, int TY, int NT, int MODE, bool EDG = false>
 __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T>& k,
                                            int tile_x, int tile_y, double dt, double alx,
                                            double aly, T* __restrict__ sm, T* __restrict__ fb,
@@ -337,7 +342,6 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
   constexpr int HR = TY + 2 * HY;     // LDS rows
   constexpr int FW = TX + 1;          // flux buffer row length
   constexpr int FR = TY + 1;          // flux buffer rows
-  constexpr bool LR = LinReg<T>::value;
   static_assert(TX * TY <= NT, "one cell per thread");
 
   const int tid = threadIdx.x;
@@ -345,6 +349,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
   const int j0 = tile_y * TY;
   const int nx = a.nx, ny = a.ny;
   const long long fs = a.fs;
+  const T hx = T(a.dx), hy = T(a.dy);
 
   // ---- stage the tile and its halo in LDS ----
   // All rounds' loads are issued before the first LDS write.
@@ -374,7 +379,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
     const int q = tid + r * NT;
     if (q < W * HR) {
 #pragma unroll
-      for (int f = 0; f < NF; ++f) sm[f * HR * W + q] = v[r][f];
+      for (int f = 0; f < NF; ++f) sm[f * HR * W + q] = staged(v[r][f], f, M, hx, hy);
     }
   }
   if constexpr (PHYS == PH_EULER) {
@@ -436,17 +441,17 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
   }
   __syncthreads();
 
-  const T idx = T(1.0 / a.dx);
-  const T hx = T(a.dx);
+  const T idx = T(1.0 / a.dx), idy = T(1.0 / a.dy);
   const bool owner = tid < TX * TY;
   const int tx = tid % TX, ty = tid / TX;
   T LU[M], LV[M], LW[M];
+  constexpr bool PROJ = PHYS == PH_EULER && MODE != MODE_COMP;
 
   // ---- x-interfaces: between local cells ix-1 and ix, ix = 0..TX ----
   for (int q = tid; q < FW * TY; q += NT) {
     const int r = q / FW, ix = q - r * FW;
     const T* row = sm + (r + HY) * W + ix;
-    auto ld = [&](int s, T* U, T* Dn, T* Dt) {
+    auto ld = [&](int s, T* U, T* Dn, T* Dt) __attribute__((always_inline)) {
 #pragma unroll
       for (int c = 0; c < M; ++c) {
         U[c] = row[(c * HR) * W + s];
@@ -454,47 +459,33 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
         if constexpr (DIM == 2) Dt[c] = row[((2 * M + c) * HR) * W + s];
       }
     };
-    // linear fluxes: their flux-buffer slots belong to this lane; the last
-    // stencil point (s = 3) completes them
-    T ha[M], xa[M];
-    auto lin = [&](int s, int c, T dh, T dx) {
-      T& h1 = fb[((M + c) * FR + r) * FW + ix];
-      T* x1 = DIM == 2 ? &fb[((2 * M + c) * FR + r) * FW + ix] : nullptr;  // 2D only
-      if constexpr (LR) {
-        if (s == 0) ha[c] = dh, xa[c] = dx;
-        else if (s < 3) ha[c] += dh, xa[c] += dx;
-        else {
-          h1 = ha[c] + dh;
-          if constexpr (DIM == 2) *x1 = xa[c] + dx;
-        }
-      } else {
-        h1 = (s == 0) ? dh : h1 + dh;
-        if constexpr (DIM == 2) *x1 = (s == 0) ? dx : *x1 + dx;
-      }
-    };
-    T fh[M];
-    interface_fluxes<T, PHYS, M, DIM == 2>(ld, lin, T(alx), hx, idx, k.ax, k, fh);
+    T fh[M], hh[M], xx[M];
+    interface_fluxes<T, PHYS, M, DIM == 2, PROJ>(ld, T(alx), k.ax, k, fh, hh, xx);
 #pragma unroll
-    for (int c = 0; c < M; ++c) fb[(c * FR + r) * FW + ix] = fh[c];
+    for (int c = 0; c < M; ++c) {
+      fb[(c * FR + r) * FW + ix] = fh[c];
+      fb[((M + c) * FR + r) * FW + ix] = hh[c];
+      if constexpr (DIM == 2) fb[((2 * M + c) * FR + r) * FW + ix] = xx[c];
+    }
   }
   __syncthreads();
+  // the interfaces' fluxes are twice f-hat, 8 h h-hat and 12 times the mixed flux
+  // of a derivative times its own cell size
   if (owner) {
 #pragma unroll
     for (int c = 0; c < M; ++c) {
       const int b0 = (c * FR + ty) * FW + tx;
-      LU[c] = -(fb[b0 + 1] - fb[b0]) * idx;
+      LU[c] = (fb[b0] - fb[b0 + 1]) * (T(0.5) * idx);
       const int b1 = ((M + c) * FR + ty) * FW + tx;
-      LV[c] = -(fb[b1 + 1] - fb[b1]) * idx;
+      LV[c] = (fb[b1] - fb[b1 + 1]) * (T(0.125) * idx * idx);
       if constexpr (DIM == 2) {
         const int b2 = ((2 * M + c) * FR + ty) * FW + tx;
-        LW[c] = -(fb[b2 + 1] - fb[b2]) * idx;
+        LW[c] = (fb[b2] - fb[b2 + 1]) * (T(1.0 / 12.0) * idx * idy);
       }
     }
   }
 
   if constexpr (DIM == 2) {
-    const T idy = T(1.0 / a.dy);
-    const T hy = T(a.dy);
     __syncthreads();
     if constexpr (EDG) {
       // Obstacle, y-interfaces: the mirror image across the top face y = oj dy
@@ -507,7 +498,7 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
     for (int q = tid; q < TX * FR; q += NT) {
       const int iy = q / TX, cc = q - iy * TX;
       const T* col = sm + iy * W + cc + 2;
-      auto ld = [&](int s, T* U, T* Dn, T* Dt) {
+      auto ld = [&](int s, T* U, T* Dn, T* Dt) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < M; ++c) {
           // normal frame: swap the two momenta; Dn = U_y, Dt = U_x
@@ -517,19 +508,14 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
           Dt[c] = col[((M + cs) * HR + s) * W];
         }
       };
-      auto lin = [&](int s, int c, T dh, T dx) {
-        const int cs = (PHYS == PH_EULER && (c == 1 || c == 2)) ? 3 - c : c;
-        T& h1 = fb[((M + cs) * FR + iy) * FW + cc];      // theta-hat -> L_W
-        h1 = (s == 0) ? dh : h1 + dh;
-        T& x1 = fb[((2 * M + cs) * FR + iy) * FW + cc];  // xi-hat -> L_V
-        x1 = (s == 0) ? dx : x1 + dx;
-      };
-      T fh[M];
-      interface_fluxes<T, PHYS, M, true>(ld, lin, T(aly), hy, idy, k.ay, k, fh);
+      T fh[M], hh[M], xx[M];
+      interface_fluxes<T, PHYS, M, true, PROJ>(ld, T(aly), k.ay, k, fh, hh, xx);
 #pragma unroll
       for (int c = 0; c < M; ++c) {
         const int cs = (PHYS == PH_EULER && (c == 1 || c == 2)) ? 3 - c : c;
         fb[(cs * FR + iy) * FW + cc] = fh[c];
+        fb[((M + cs) * FR + iy) * FW + cc] = hh[c];      // theta-hat -> L_W
+        fb[((2 * M + cs) * FR + iy) * FW + cc] = xx[c];  // xi-hat -> L_V
       }
     }
     __syncthreads();
@@ -537,11 +523,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
 #pragma unroll
       for (int c = 0; c < M; ++c) {
         const int b0 = (c * FR + ty) * FW + tx;
-        LU[c] -= (fb[b0 + FW] - fb[b0]) * idy;
+        LU[c] = mad(fb[b0] - fb[b0 + FW], T(0.5) * idy, LU[c]);
         const int b1 = ((M + c) * FR + ty) * FW + tx;
-        LW[c] -= (fb[b1 + FW] - fb[b1]) * idy;
+        LW[c] = mad(fb[b1] - fb[b1 + FW], T(0.125) * idy * idy, LW[c]);
         const int b2 = ((2 * M + c) * FR + ty) * FW + tx;
-        LV[c] -= (fb[b2 + FW] - fb[b2]) * idy;
+        LV[c] = mad(fb[b2] - fb[b2 + FW], T(1.0 / 12.0) * idx * idy, LV[c]);
       }
     }
   }
@@ -571,63 +557,64 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
   } else {
     // S^_k = (U_k, limited derivatives of S_k)
     T Sh[NF];
-    constexpr bool charlim = CL && PHYS == PH_EULER;
+    const bool charlim = PHYS == PH_EULER && (MODE == MODE_CHAR_LIM || (MODE == MODE_COMP && k.limiter_char));
     const bool complim = k.limiter_on && !charlim;
     // the x-neighbour of a fluid cell next to the obstacle's front face is that
     // cell's own mirror image (the stage buffer holds the y-image there)
     bool front = false;
     if constexpr (EDG) front = gi == e->oi - 1 && gj < e->oj;
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
+    // differences of one cell's x- or y-stencil (limit_blend), d = 0 or 1
+    auto stencil = [&](int c, int d, T& d1, T& d2, T& vs, T& vd) __attribute__((always_inline)) {
       const T* u = own + (c * HR) * W;
-      const T* v = own + ((M + c) * HR) * W;
-      Sh[c] = u[0];
-      T up = u[1], vp = v[1];
+      const T* v = own + (((1 + d) * M + c) * HR) * W;
+      const int st = d == 0 ? 1 : W;
+      T up = u[st], vp = v[st];
       if constexpr (EDG) {
-        if (front) {
+        if (d == 0 && front) {
           up = mirror_sign(c, M, true, 0) < 0 ? -u[0] : u[0];
           vp = mirror_sign(M + c, M, true, 0) < 0 ? -v[0] : v[0];
         }
       }
-      Sh[M + c] = complim ? limit1(u[-1], u[0], up, v[-1], vp, hx, idx, k.lw) : v[0];
-      if constexpr (DIM == 2) {
-        const T* w = own + ((2 * M + c) * HR) * W;
-        Sh[2 * M + c] = complim ? limit1(u[-W], u[0], u[W], w[-W], w[W], T(a.dy),
-                                         T(1.0 / a.dy), k.lw)
-                                : w[0];
+      const T vm = v[-st];
+      d1 = u[0] - u[-st], d2 = up - u[0];
+      vs = vm + vp, vd = vm - vp;
+    };
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+      Sh[c] = own[(c * HR) * W];
+      if (complim) {
+        T d1, d2, vs, vd;
+        stencil(c, 0, d1, d2, vs, vd);
+        Sh[M + c] = idx * mad(T(0.5), d1 + d2, limit_blend(d1, d2, vs, vd, k.lb));
+        if constexpr (DIM == 2) {
+          stencil(c, 1, d1, d2, vs, vd);
+          Sh[2 * M + c] = idy * mad(T(0.5), d1 + d2, limit_blend(d1, d2, vs, vd, k.lb));
+        }
+      } else if (!k.limiter_on) {
+        // unlimited: the derivatives themselves, not their scaled copies
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) Sh[(1 + d) * M + c] = gld(a.in + ((1 + d) * M + c) * fs + g);
       }
     }
-    if constexpr (charlim) {
-      if (k.limiter_on) {
+    if constexpr (PHYS == PH_EULER && MODE != MODE_CHAR) {
+      if (charlim && k.limiter_on) {
         // characteristic variant of the limiter, x then y (normal frame:
         // the two momenta swap places for y)
-        T um[M], u0[M], up[M], vm[M], vp[M], r[M];
 #pragma unroll
-        for (int c = 0; c < M; ++c) {
-          const T* u = own + (c * HR) * W;
-          const T* v = own + ((M + c) * HR) * W;
-          um[c] = u[-1], u0[c] = u[0], up[c] = u[1], vm[c] = v[-1], vp[c] = v[1];
-          if constexpr (EDG) {
-            if (front) {
-              up[c] = mirror_sign(c, M, true, 0) < 0 ? -u[0] : u[0];
-              vp[c] = mirror_sign(M + c, M, true, 0) < 0 ? -v[0] : v[0];
-            }
-          }
-        }
-        limit_char<T, M>(um, u0, up, vm, vp, hx, idx, k.lw, k.gm1, r);
-#pragma unroll
-        for (int c = 0; c < M; ++c) Sh[M + c] = r[c];
-        if constexpr (DIM == 2) {
+        for (int d = 0; d < DIM; ++d) {
+          T u0[M], d1[M], d2[M], vs[M], vd[M], r[M];
 #pragma unroll
           for (int c = 0; c < M; ++c) {
-            const int q = (c == 1) ? 2 : (c == 2) ? 1 : c;
-            const T* u = own + (q * HR) * W;
-            const T* w = own + ((2 * M + q) * HR) * W;
-            um[c] = u[-W], u0[c] = u[0], up[c] = u[W], vm[c] = w[-W], vp[c] = w[W];
+            const int q = (d == 1 && (c == 1 || c == 2)) ? 3 - c : c;
+            u0[c] = own[(q * HR) * W];
+            stencil(q, d, d1[c], d2[c], vs[c], vd[c]);
           }
-          limit_char<T, M>(um, u0, up, vm, vp, T(a.dy), T(1.0 / a.dy), k.lw, k.gm1, r);
+          limit_char_d<T, M>(u0, d1, d2, vs, vd, k.lb, k.gm1, r);
 #pragma unroll
-          for (int c = 0; c < M; ++c) Sh[2 * M + ((c == 1) ? 2 : (c == 2) ? 1 : c)] = r[c];
+          for (int c = 0; c < M; ++c) {
+            const int q = (d == 1 && (c == 1 || c == 2)) ? 3 - c : c;
+            Sh[(1 + d) * M + q] = (d == 0 ? idx : idy) * r[c];
+          }
         }
       }
     }
@@ -670,16 +657,17 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
 // ---------------------------------------------------------------------------
 // Resident waves per SIMD the stage kernels are compiled for (the register
 // budget is 512 / WAVES per lane; LDS allows five FP32 and two FP64
-// workgroups per CU).  Runge-Kutta stages: five waves in FP32 (96 VGPRs),
-// two in FP64.  The right-hand-side-only FP32 kernel (K = 0) keeps three:
-// at four it spills and runs 4 % slower; the FP64 one runs two waves with a
-// small spill, 30 % faster than at one wave.
+// workgroups per CU).  FP32: four, where every stage kernel fits (104-108
+// VGPRs); at five (96) they spill 40 B per lane: 2.583 against 2.606 ms for
+// four steps of 2047 x 1531, and 5.09 against 5.65 ms for a step of 256
+// batched grids, whose persistent kernel spills most.  FP64: two (218 VGPRs,
+// no spills); a third would need 168 and spills 352 B.
 template <typename T, int K>
 struct StageOcc {
-  static constexpr int WAVES = sizeof(T) == 4 ? (K == 0 ? 3 : 5) : 2;
+  static constexpr int WAVES = sizeof(T) == 4 ? 4 : 2;
 };
 
-template <typename T, int PHYS, int DIM, int K, int TX, int TY, int NT, bool CL>
+template <typename T, int PHYS, int DIM, int K, int TX, int TY, int NT, int MODE>
 __global__ __launch_bounds__(NT, (StageOcc<T, K>::WAVES)) void k_stage(StageArgs<T> a, Consts<T> k) {
   constexpr int M = Comps<PHYS, DIM>::M;
   constexpr int NF = Comps<PHYS, DIM>::NF;
@@ -704,7 +692,7 @@ __global__ __launch_bounds__(NT, (StageOcc<T, K>::WAVES)) void k_stage(StageArgs
   const int tile_y = t / ntx, tile_x = t - tile_y * ntx;
   T sx = T(0), sy = T(0);
   uint32_t flags = 0;
-  stage_tile<T, PHYS, DIM, K, TX, TY, NT, CL>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb, sx, sy,
+  stage_tile<T, PHYS, DIM, K, TX, TY, NT, MODE>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb, sx, sy,
                                               flags);
   if constexpr (K > 0) {
     // speeds of the new stage state feed the next stage's splitting; after
@@ -714,7 +702,7 @@ __global__ __launch_bounds__(NT, (StageOcc<T, K>::WAVES)) void k_stage(StageArgs
   }
 }
 
-// 2D Euler with edge-described sides (CL: the characteristic limiter).  The body
+// 2D Euler with edge-described sides.  The body
 // repeats k_stage's: handing the kernel parameters to a shared device
 // function by reference costs k_stage its register allocation (spills).
 // Three waves per SIMD in FP32: at five the boundary fix-up spills.
@@ -723,7 +711,7 @@ struct EdgeOcc {
   static constexpr int WAVES = sizeof(T) == 4 ? 3 : 2;
 };
 
-template <typename T, int K, int TX, int TY, int NT, bool CL>
+template <typename T, int K, int TX, int TY, int NT, int MODE>
 __global__ __launch_bounds__(NT, (EdgeOcc<T>::WAVES)) void k_stage_edges(StageArgs<T> a,
                                                                              Consts<T> k,
                                                                              EdgeArgs e) {
@@ -751,7 +739,7 @@ __global__ __launch_bounds__(NT, (EdgeOcc<T>::WAVES)) void k_stage_edges(StageAr
   const int tile_y = t / ntx, tile_x = t - tile_y * ntx;
   T sx = T(0), sy = T(0);
   uint32_t flags = 0;
-  stage_tile<T, PH_EULER, 2, K, TX, TY, NT, CL, true>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb,
+  stage_tile<T, PH_EULER, 2, K, TX, TY, NT, MODE, true>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb,
                                                       sx, sy, flags, &e);
   if constexpr (K > 0) {
     // speeds of the new stage state feed the next stage's splitting; after
@@ -806,7 +794,7 @@ __device__ __forceinline__ StageArgs<T> instance_args(const hweno_instance& I, d
 
 // One tile t of the flattened list; nothing is done when its instance's step
 // is skipped (a decision uniform over the workgroup).
-template <typename T, int V, int K, bool CL>
+template <typename T, int V, int K, int MODE>
 __device__ __forceinline__ void batched_tile(const hweno_instance* __restrict__ inst,
                                              const int* __restrict__ tile_map, int t, double cfl,
                                              const Consts<T>& k, T* sm, T* fb) {
@@ -823,7 +811,7 @@ __device__ __forceinline__ void batched_tile(const hweno_instance* __restrict__ 
   const int tile_y = lt / ntx, tile_x = lt - tile_y * ntx;
   T sx = T(0), sy = T(0);
   uint32_t flags = 0;
-  stage_tile<T, PH_EULER, 2, K, TX, TY, NT, CL>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb, sx,
+  stage_tile<T, PH_EULER, 2, K, TX, TY, NT, MODE>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb, sx,
                                                 sy, flags);
   block_fold<NT>(double(sx), double(sy), flags, a.ctrl + 2 * K, a.status, K < 3);
 }
@@ -833,7 +821,7 @@ __device__ __forceinline__ void batched_tile(const hweno_instance* __restrict__ 
 // those reads stay scalar and never queue behind the other workgroups'
 // atomics on the same control line.  Otherwise: persistent, striding over
 // XCD bands of the tile list.
-template <typename T, int V, int K, bool ONE, bool CL>
+template <typename T, int V, int K, bool ONE, int MODE>
 __global__ __launch_bounds__(256, (StageOcc<T, K>::WAVES)) void k_stage_batched(
     const hweno_instance* __restrict__ inst, const int* __restrict__ tile_map, int total,
     double cfl, Consts<T> k) {
@@ -841,11 +829,11 @@ __global__ __launch_bounds__(256, (StageOcc<T, K>::WAVES)) void k_stage_batched(
   __shared__ T sm[12 * (TY + 4) * (TX + 4)];
   __shared__ T fb[12 * (TY + 1) * (TX + 1)];
   if constexpr (ONE) {
-    batched_tile<T, V, K, CL>(inst, tile_map, xcd_band(blockIdx.x, gridDim.x), cfl, k, sm, fb);
+    batched_tile<T, V, K, MODE>(inst, tile_map, xcd_band(blockIdx.x, gridDim.x), cfl, k, sm, fb);
   } else {
     const BandIter bi(total);
     for (int it = 0; bi.valid(it); ++it) {
-      batched_tile<T, V, K, CL>(inst, tile_map, bi.tile(it), cfl, k, sm, fb);
+      batched_tile<T, V, K, MODE>(inst, tile_map, bi.tile(it), cfl, k, sm, fb);
       __syncthreads();  // LDS tile and fold slots are reused by the next tile
     }
   }
@@ -1867,12 +1855,25 @@ Consts<T> make_consts(const hweno_problem* p) {
   k.characteristic = p->characteristic ? 1 : 0;
   k.limiter_on = p->limiter_on ? 1 : 0;
   k.limiter_char = p->limiter_characteristic ? 1 : 0;
+  k.rb = recon_blend(T(p->lin_w[1]), T(p->lin_w[2]), T(p->eps));
+  k.lb = limit_blend_weights(T(p->lim_w[1]), T(p->lim_w[2]), T(p->eps));
   return k;
 }
 
 // the characteristic limiter variant is in force (Euler with the limiter on)
 bool char_limiter(const hweno_problem* p) {
   return p->physics == HWENO_EULER && p->limiter_on && p->limiter_characteristic;
+}
+
+// calls f(integral constant) with the stage kernels' MODE for an Euler problem
+template <typename F>
+void with_mode(const hweno_problem* p, F&& f) {
+  if (!p->characteristic)
+    f(std::integral_constant<int, MODE_COMP>{});
+  else if (char_limiter(p))
+    f(std::integral_constant<int, MODE_CHAR_LIM>{});
+  else
+    f(std::integral_constant<int, MODE_CHAR>{});
 }
 
 hweno_status launch_check(const char* what) {
@@ -1997,15 +1998,23 @@ struct RunRhs {
     a.out = (T*)rhs;
     a.alpha = alpha;
     constexpr int TX = Tile<DIM>::TX, TY = Tile<DIM>::TY, NT = Tile<DIM>::NT;
-    if constexpr (PHYS == PH_EULER && DIM == 2) {
-      if (has_edges(p)) {
-        k_stage_edges<T, 0, TX, TY, NT, false><<<stage_grid(DIM, a.nx, a.ny), NT, 0, s>>>(
-            a, make_consts<T>(p), edge_args(p));
-        return launch_check("rhs");
+    const dim3 grid = stage_grid(DIM, a.nx, a.ny);
+    const Consts<T> k = make_consts<T>(p);
+    // the limiter plays no part in the right-hand side
+    auto launch = [&](auto mode) {
+      constexpr int MODE = decltype(mode)::value;
+      if constexpr (PHYS == PH_EULER && DIM == 2) {
+        if (has_edges(p)) {
+          k_stage_edges<T, 0, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k, edge_args(p));
+          return;
+        }
       }
-    }
-    k_stage<T, PHYS, DIM, 0, TX, TY, NT, false><<<stage_grid(DIM, a.nx, a.ny), NT, 0, s>>>(
-        a, make_consts<T>(p));
+      k_stage<T, PHYS, DIM, 0, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k);
+    };
+    if (PHYS == PH_EULER && p->characteristic)
+      launch(std::integral_constant<int, PHYS == PH_EULER ? MODE_CHAR : MODE_COMP>{});
+    else
+      launch(std::integral_constant<int, MODE_COMP>{});
     return launch_check("rhs");
   }
 };
@@ -2085,48 +2094,42 @@ struct RunStep {
     T* s2 = (T*)b.s2;
     constexpr int TX = Tile<DIM>::TX, TY = Tile<DIM>::TY, NT = Tile<DIM>::NT;
     const dim3 grid = stage_grid(DIM, a.nx, a.ny);
-    auto stages = [&](auto cl) {
-      constexpr bool CL = decltype(cl)::value;
+    auto stages = [&](auto mode) {
+      constexpr int MODE = decltype(mode)::value;
       a.in = (const T*)state;
       a.out = s1;
-      timed(s, [&] { k_stage<T, PHYS, DIM, 1, TX, TY, NT, CL><<<grid, NT, 0, s>>>(a, k); });
+      timed(s, [&] { k_stage<T, PHYS, DIM, 1, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k); });
       a.in = s1;
       a.out = s2;
-      timed(s, [&] { k_stage<T, PHYS, DIM, 2, TX, TY, NT, CL><<<grid, NT, 0, s>>>(a, k); });
+      timed(s, [&] { k_stage<T, PHYS, DIM, 2, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k); });
       a.in = s2;
       a.out = (T*)state;
-      timed(s, [&] { k_stage<T, PHYS, DIM, 3, TX, TY, NT, CL><<<grid, NT, 0, s>>>(a, k); });
+      timed(s, [&] { k_stage<T, PHYS, DIM, 3, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k); });
     };
     if constexpr (PHYS == PH_EULER) {
       if constexpr (DIM == 2) {
         if (has_edges(p)) {
           const EdgeArgs e = edge_args(p);
-          auto edge_stages = [&](auto cl) {
-            constexpr bool CLE = decltype(cl)::value;
+          auto edge_stages = [&](auto mode) {
+            constexpr int MODE = decltype(mode)::value;
             a.in = (const T*)state;
             a.out = s1;
-            timed(s, [&] { k_stage_edges<T, 1, TX, TY, NT, CLE><<<grid, NT, 0, s>>>(a, k, e); });
+            timed(s, [&] { k_stage_edges<T, 1, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k, e); });
             a.in = s1;
             a.out = s2;
-            timed(s, [&] { k_stage_edges<T, 2, TX, TY, NT, CLE><<<grid, NT, 0, s>>>(a, k, e); });
+            timed(s, [&] { k_stage_edges<T, 2, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k, e); });
             a.in = s2;
             a.out = (T*)state;
-            timed(s, [&] { k_stage_edges<T, 3, TX, TY, NT, CLE><<<grid, NT, 0, s>>>(a, k, e); });
+            timed(s, [&] { k_stage_edges<T, 3, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k, e); });
           };
-          if (char_limiter(p))
-            edge_stages(std::true_type{});
-          else
-            edge_stages(std::false_type{});
+          with_mode(p, edge_stages);
           k_finish<<<1, 64, 0, s>>>(ctrl, tape, fold_next && !replay ? 1 : 0);
           return launch_check("rk3_step");
         }
       }
-      if (char_limiter(p))
-        stages(std::true_type{});
-      else
-        stages(std::false_type{});
+      with_mode(p, stages);
     } else {
-      stages(std::false_type{});
+      stages(std::integral_constant<int, MODE_COMP>{});
     }
     k_finish<<<1, 64, 0, s>>>(ctrl, tape, fold_next && !replay ? 1 : 0);
     return launch_check("rk3_step");
@@ -2309,7 +2312,7 @@ int batched_grid(int blocks, int total) {
   int grid = blocks;
   if (grid <= 0) {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_stage_batched<T, V, 1, false, false>, 256, 0) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_stage_batched<T, V, 1, false, MODE_CHAR>, 256, 0) !=
             hipSuccess ||
         per_cu < 1)
       per_cu = 1;
@@ -2326,24 +2329,19 @@ hweno_status run_batched(const hweno_problem* p, const hweno_instance* inst, con
   const unsigned small = (unsigned)((n + 255) / 256);
   k_begin_batched<<<small, 256, 0, s>>>(inst, n);
   k_alpha_batched<T, V><<<std::min(total, 4 * device_cus()), 256, 0, s>>>(inst, map, total, k);
-  auto stages = [&](auto one, auto cl) {
-    constexpr bool ONE = decltype(one)::value, CL = decltype(cl)::value;
-    timed(s, [&] { k_stage_batched<T, V, 1, ONE, CL><<<grid, 256, 0, s>>>(inst, map, total, p->cfl, k); });
-    timed(s, [&] { k_stage_batched<T, V, 2, ONE, CL><<<grid, 256, 0, s>>>(inst, map, total, p->cfl, k); });
-    timed(s, [&] { k_stage_batched<T, V, 3, ONE, CL><<<grid, 256, 0, s>>>(inst, map, total, p->cfl, k); });
-  };
-  const bool cl = char_limiter(p);
-  if (grid == total) {
-    if (cl)
-      stages(std::true_type{}, std::true_type{});
+  with_mode(p, [&](auto mode) {
+    constexpr int MODE = decltype(mode)::value;
+    auto stages = [&](auto one) {
+      constexpr bool ONE = decltype(one)::value;
+      timed(s, [&] { k_stage_batched<T, V, 1, ONE, MODE><<<grid, 256, 0, s>>>(inst, map, total, p->cfl, k); });
+      timed(s, [&] { k_stage_batched<T, V, 2, ONE, MODE><<<grid, 256, 0, s>>>(inst, map, total, p->cfl, k); });
+      timed(s, [&] { k_stage_batched<T, V, 3, ONE, MODE><<<grid, 256, 0, s>>>(inst, map, total, p->cfl, k); });
+    };
+    if (grid == total)
+      stages(std::true_type{});
     else
-      stages(std::true_type{}, std::false_type{});
-  } else {
-    if (cl)
-      stages(std::false_type{}, std::true_type{});
-    else
-      stages(std::false_type{}, std::false_type{});
-  }
+      stages(std::false_type{});
+  });
   k_finish_batched<<<small, 256, 0, s>>>(inst, n);
   return launch_check("rk3_step_batched");
 }
