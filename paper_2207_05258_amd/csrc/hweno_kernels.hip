@@ -585,10 +585,10 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
       if (complim) {
         T d1, d2, vs, vd;
         stencil(c, 0, d1, d2, vs, vd);
-        Sh[M + c] = idx * mad(T(0.5), d1 + d2, limit_blend(d1, d2, vs, vd, k.lb));
+        Sh[M + c] = idx * limit_blend(d1, d2, vs, vd, k.lb);
         if constexpr (DIM == 2) {
           stencil(c, 1, d1, d2, vs, vd);
-          Sh[2 * M + c] = idy * mad(T(0.5), d1 + d2, limit_blend(d1, d2, vs, vd, k.lb));
+          Sh[2 * M + c] = idy * limit_blend(d1, d2, vs, vd, k.lb);
         }
       } else if (!k.limiter_on) {
         // unlimited: the derivatives themselves, not their scaled copies
@@ -1056,39 +1056,39 @@ struct AdjArgs {
   FoldArgs<T> fo;
 };
 
-// a lane's column of an LDS buffer, read as an array
-template <typename T>
-struct Col {
-  const T* p;
-  int stride;
-  __device__ T operator[](int c) const { return p[c * stride]; }
-};
+constexpr int cmax(int x, int y) { return x > y ? x : y; }
 
+// FP32 fits four waves per SIMD (126 VGPRs, 38 KB of LDS per workgroup), FP64
+// two (235 VGPRs, 77 KB), both without spills.
 template <typename T>
 struct AdjOcc {
-  static constexpr int WAVES = sizeof(T) == 4 ? 3 : 1;
+  static constexpr int WAVES = sizeof(T) == 4 ? 4 : 2;
 };
-
-constexpr int cmax(int x, int y) { return x > y ? x : y; }
 
 // One output tile of E per workgroup (TX x TY entries, ghost entries
 // included).  Every interface and limiter stencil that touches the tile is
-// differentiated by one lane.  Its contributions to the stencil's cells are
-// handed over point by point: at each emit every lane writes the values for
-// one stencil point (or one group of points) into its own column of a small
-// LDS buffer, and after a barrier the owner of each output entry adds the
-// column that points at it to its accumulators, one LDS slot per field and entry
-// (held in registers they made the kernel spill).
-// No atomics, and the buffer holds one point's contributions instead of a
-// whole stencil's, so several workgroups fit on a compute unit.  The barriers
-// also keep the compiler from holding the staged stencil in registers across
-// the reverse pass (loads after a barrier are reloads).  Lanes without an
-// interface or with a zero adjoint run the same code on a valid stencil (every
-// lane takes part in every barrier) and emit exact zeros.  The state tile is
-// staged cell-interleaved ([row][col][field]) so that one stencil point's
-// fields are read with a few wide LDS loads.
-// CL: the characteristic limiter variant (Euler), a separate instantiation.
-template <typename T, int PHYS, int DIM, int TX, int TY, int NT, bool CL>
+// differentiated by one lane.
+// The data of a cell enter its interfaces only through x+- = F +- alpha U and
+// y+- = A Dn +- alpha Dn (interface_fluxes), so the interfaces' lanes add their
+// adjoints of x+-, y+- to the cells' sums in LDS and the owner of each cell takes
+// the sums through the point fluxes once per direction, instead of every
+// interface and side doing so for each of its points.  The linear fluxes'
+// adjoints are stencils of the incoming one: each lane leaves its interface's in
+// LDS and the owners apply the four coefficients.
+// The additions go point by point: in one phase all lanes add to stencil point s of
+// their interfaces, which are distinct cells, and a barrier ends the phase.  So
+// the sums need no atomics and have a fixed order.  The barriers also keep
+// the compiler from holding the staged stencil in registers (loads after a
+// barrier are reloads).  Lanes without an interface or with a zero adjoint run
+// the same code on a valid stencil (every lane takes part in every barrier) and add
+// nothing.  The state tile is staged cell-interleaved ([row][col][field],
+// derivatives times their cell size) so that one stencil point's fields are read
+// with a few wide LDS loads.
+// Measured (one launch under the profiler): with every interface reversing the point
+// fluxes of its six point data itself and handing 12 fields over per point, 512^2
+// FP32 took 116 us (9278 VALU instructions per lane) and 128^2 FP64 47 us; in this
+// form 79 us (6100) and 35 us.
+template <typename T, int PHYS, int DIM, int TX, int TY, int NT, int MODE>
 __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, Consts<T> k) {
   constexpr int M = Comps<PHYS, DIM>::M;
   constexpr int NF = Comps<PHYS, DIM>::NF;
@@ -1099,13 +1099,16 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
   constexpr int NIY = (DIM == 2) ? TX * (TY + 3) : 0;  // y-interfaces
   constexpr int NLX = TY * (TX + 2);                   // cells whose x-limiter touches it
   constexpr int NLY = (DIM == 2) ? TX * (TY + 2) : 0;
-  constexpr int NR = cmax(NF, 3 * M);                  // rows of the hand-over buffer
+  constexpr int AS = TX * TY;                          // stride of the sums' fields
+  constexpr int NG = DIM == 2 ? 2 * M : M;             // linear fluxes' adjoints of an interface
+  constexpr bool EU = PHYS == PH_EULER;
+  constexpr bool PROJ = EU && MODE != MODE_COMP;
   static_assert(TX * TY <= NT, "one output entry per thread");
   static_assert(NIX <= NT && NIY <= NT && NLX <= NT && NLY <= NT, "one stencil per lane");
   __shared__ __align__(16) T sm[HR * W * NF];
-  __shared__ T pt[NR * NT];
-  __shared__ T accs[NF * TX * TY];
-  __shared__ T gin[2 * M * NT];  // this lane's adjoints of h-hat and of the mixed flux
+  __shared__ T accs[NF * AS];                          // adjoint of the cells' fields
+  // the linear fluxes' adjoints by interface, then the sums of gx, gy by cell
+  __shared__ T pool[cmax(NG * NT, 2 * M * AS)];
   const int nx = a.nx, ny = a.ny;
   const long long fs = a.fs;
   const int ntx = (a.nxe + TX - 1) / TX;
@@ -1115,6 +1118,7 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
   const int tid = threadIdx.x;
   const T cr = T(a.cr * (a.dtp ? *a.dtp : 1.0));
   const T cl = T(a.cl);
+  const T idx = T(1.0 / a.dx), hx = T(a.dx), idy = T(1.0 / a.dy), hy = T(a.dy);
   for (int q = tid; q < W * HR; q += NT) {
     const int lr = q / W, lc = q - lr * W;
     const int ii = rx0 - HX + lc, jj = ry0 - HY + lr;
@@ -1122,309 +1126,294 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
     const int gj = (DIM == 2) ? map_index(jj, ny, a.bc_y) : 0;
     const long long g = (long long)gj * nx + gi;
     const bool mx = mirrored(ii, nx, a.bc_x), my = DIM == 2 && mirrored(jj, ny, a.bc_y);
+    T x[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) x[f] = gld(a.S + f * fs + g);
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-      const T x = a.S[f * fs + g];
-      const int sg = (mx ? mirror_sign(f, M, PHYS == PH_EULER, 0) : 1) *
-                     (my ? mirror_sign(f, M, PHYS == PH_EULER, 1) : 1);
-      sm[q * NF + f] = sg < 0 ? -x : x;
+      const int sg = (mx ? mirror_sign(f, M, EU, 0) : 1) * (my ? mirror_sign(f, M, EU, 1) : 1);
+      sm[q * NF + f] = staged(sg < 0 ? -x[f] : x[f], f, M, hx, hy);
     }
   }
-  __syncthreads();
 
   auto xl = [&](int f, int i, int j) -> T {
-    return (i >= 0 && i < nx && j >= 0 && j < ny) ? a.XL[f * fs + (long long)j * nx + i] : T(0);
+    return (i >= 0 && i < nx && j >= 0 && j < ny) ? gld(a.XL + f * fs + (long long)j * nx + i) : T(0);
   };
   // cell (i, j) of the staged state
   auto cell = [&](int i, int j) -> const T* {
     return sm + ((j - (ry0 - HY)) * W + (i - (rx0 - HX))) * NF;
   };
-  const bool owner = tid < TX * TY;
+  const bool owner = tid < AS;
   const int lx = tid % TX, ly = tid / TX;
-  const T idx = T(1.0 / a.dx), hx = T(a.dx);
   T* acc = accs + (owner ? tid : 0);
-  constexpr int AS = TX * TY;  // stride of the accumulator fields
   if (owner) {
 #pragma unroll
     for (int f = 0; f < NF; ++f) acc[f * AS] = T(0);
   }
-  // row r of this lane's column of the hand-over buffer
-  auto put = [&](int r, T v) { pt[r * NT + tid] = v; };
-  auto col = [&](int r, int q) -> T { return pt[r * NT + q]; };
 
-  // ---- x-interfaces I (between cells I and I+1) that touch the tile ----
-  {
+  // ---- interfaces along direction d (0: x, 1: y) that touch the tile ----
+  // interface q lies between points 1 and 2 of its stencil; its point s is the
+  // tile's cell (sx + s, sy) along x, (sx, sy + s) along y
+  auto direction = [&](auto dir) __attribute__((always_inline)) {
+    constexpr int d = decltype(dir)::value;
+    constexpr int NI = d == 0 ? NIX : NIY;
+    constexpr int ST = d == 0 ? NF : W * NF;     // LDS step along the direction
+    constexpr int CS = d == 0 ? 1 : TX;          // step of the tile's cells
+    constexpr int ON = (1 + d) * M, OT = (2 - d) * M;  // normal and tangential derivatives
+    // component c of the normal frame (normal momentum first)
+    auto cs = [](int c) { return (EU && d == 1 && (c == 1 || c == 2)) ? 3 - c : c; };
+    const T ihn = d == 0 ? idx : idy, iht = d == 0 ? idy : idx;
+    const T alpha = T(a.alpha[d]), an = d == 0 ? k.ax : k.ay;
     // lanes past the last interface take the last one, with a zero adjoint
-    const int q = tid < NIX ? tid : NIX - 1;
-    const int r = q / (TX + 3), ii = q - r * (TX + 3);
-    const int j = ry0 + r, I = rx0 - 2 + ii;
-    T gf[M], gh[M], gx[M];
+    const int q = tid < NI ? tid : NI - 1;
+    const int qr = d == 0 ? q / (TX + 3) : q / TX;
+    const int qc = d == 0 ? q - qr * (TX + 3) : q - qr * TX;
+    const int sx = d == 0 ? qc - 3 : qc, sy = d == 0 ? qr : qr - 3;
+    const int i1 = rx0 + sx + (d == 0 ? 1 : 0), j1 = ry0 + sy + (d == 1 ? 1 : 0);  // point 1
+    const int i2 = i1 + (d == 0 ? 1 : 0), j2 = j1 + (d == 1 ? 1 : 0);
+    const bool live = tid < NI && (d == 0 ? (j1 >= 0 && j1 < ny && i1 >= -1 && i1 <= nx - 1)
+                                          : (i1 >= 0 && i1 < nx && j1 >= -1 && j1 <= ny - 1));
+    T gf[M];
     bool any = false;
-    const bool live = tid < NIX && j >= 0 && j < ny && I >= -1 && I <= nx - 1;
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-      gf[c] = live ? cr * (xl(c, I + 1, j) - xl(c, I, j)) * idx : T(0);
-      gh[c] = live ? cr * (xl(M + c, I + 1, j) - xl(M + c, I, j)) * idx : T(0);
-      gx[c] = (DIM == 2 && live) ? cr * (xl(2 * M + c, I + 1, j) - xl(2 * M + c, I, j)) * idx : T(0);
-      any = any || gf[c] != T(0) || gh[c] != T(0) || gx[c] != T(0);
-    }
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-      gin[c * NT + tid] = gh[c];
-      gin[(M + c) * NT + tid] = gx[c];
-    }
-    const Col<T> ghc{gin + tid, NT}, gxc{gin + M * NT + tid, NT};
-    const T* row = cell(I - 1, j);
-    auto ld = [&](int s, T* U, T* Dn, T* Dt) {
-      const T* p = row + s * NF;
+    {
+      T gh[M], gx[M];
 #pragma unroll
       for (int c = 0; c < M; ++c) {
-        U[c] = p[c];
-        Dn[c] = p[M + c];
-        Dt[c] = (DIM == 2) ? p[2 * M + c] : T(0);
+        // adjoints of 2 f-hat, 8 h h-hat and 12 times the scaled mixed flux
+        auto diff = [&](int f) { return live ? cr * (xl(f, i2, j2) - xl(f, i1, j1)) * ihn : T(0); };
+        gf[c] = T(0.5) * diff(cs(c));
+        gh[c] = (T(0.125) * ihn) * diff(ON + cs(c));
+        gx[c] = DIM == 2 ? (T(1.0 / 12.0) * iht) * diff(OT + cs(c)) : T(0);
+        any = any || gf[c] != T(0) || gh[c] != T(0) || gx[c] != T(0);
       }
-    };
-    // entry (lx, ly) is point s of interface ii = lx + 3 - s in its row
-    const int qo = ly * (TX + 3) + lx + 3;
-    auto emit = [&](int s, int mode, const T* gU, const T* gDn, const T* gDt) {
-      if (mode == EMIT_ADD_U) {
-        // the Roe-average contributions to points 1 and 2 share one hand-over
 #pragma unroll
-        for (int c = 0; c < M; ++c) put((s == 1 ? 0 : M) + c, any ? gU[c] : T(0));
-        if (s == 1) return;
-      } else {
+      for (int c = 0; c < M; ++c) {
+        pool[c * NT + tid] = gh[c];
+        if constexpr (DIM == 2) pool[(M + c) * NT + tid] = gx[c];
+      }
+    }
+    __syncthreads();
+    // the cell's own state in the normal frame
+    const T* own = sm + (((owner ? ly : 0) + HY) * W + (owner ? lx : 0) + HX) * NF;
+    auto ld = [&](const T* p, T* U, T* Dn) __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) U[c] = p[cs(c)], Dn[c] = p[ON + cs(c)];
+    };
+    // adjoint of the cell's fields (normal frame), nothing when it is zero
+    auto add_cell = [&](const T* gU, const T* gN) __attribute__((always_inline)) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) acc[cs(c) * AS] += gU[c], acc[(ON + cs(c)) * AS] += gN[c];
+    };
+    T lF[M], lA[M];
+    if (owner) {
+      // linear fluxes: the cell is point s of interface q0 + (3 - s) CS
+      const int q0 = d == 0 ? ly * (TX + 3) + lx : ly * TX + lx;
+      T gU[M], gN[M], gT[M], gB[M];
+      bool some = false, mixed = false;
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        const T* g = pool + c * NT + q0;
+        const T p3 = g[0], p2 = g[CS], p1 = g[2 * CS], p0 = g[3 * CS];
+        lF[c] = mad(T(15), p2 - p1, p0 - p3);
+        lA[c] = T(1.0 / 3.0) * mad(T(-7), p1 + p2, p0 + p3);
+        // U and Dn themselves, less what the sums of x+ and y+, which start from
+        // lF and lA, will add
+        gU[c] = alpha * ((p0 + p3) - (p1 + p2) - lF[c]);
+        gN[c] = alpha * mad(T(1.0 / 3.0), mad(T(3), p1 - p2, p0 - p3), -lA[c]);
+        some = some || p0 != T(0) || p1 != T(0) || p2 != T(0) || p3 != T(0);
+        gT[c] = T(0);
+        if constexpr (DIM == 2) {
+          const T* x = g + M * NT;
+          gB[c] = mad(T(7), x[CS] + x[2 * CS], -(x[0] + x[3 * CS]));
+          mixed = mixed || gB[c] != T(0);
+        }
+      }
+      if (some) add_cell(gU, gN);
+      if constexpr (DIM == 2) {
+        if (mixed) {
+          T U[M], Dt[M];
+#pragma unroll
+          for (int c = 0; c < M; ++c) U[c] = own[cs(c)], Dt[c] = own[OT + cs(c)], gU[c] = T(0);
+          point_fluxes_vjp<T, PHYS, M, true, false>(U, Dt, Dt, k, an, nullptr, nullptr, gB, gU, gT, gT);
+#pragma unroll
+          for (int c = 0; c < M; ++c) acc[cs(c) * AS] += gU[c], acc[(OT + cs(c)) * AS] += gT[c];
+        }
+      }
+    }
+    __syncthreads();
+    if (owner) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) pool[c * AS + tid] = lF[c], pool[(M + c) * AS + tid] = lA[c];
+    }
+    // ---- the nonlinear flux, "+" side then "-" side ----
+    const T* base = cell(i1 - (d == 0 ? 1 : 0), j1 - (d == 1 ? 1 : 0));
+    auto lds = [&](int s, T* U, T* Dn) __attribute__((always_inline)) { ld(base + s * ST, U, Dn); };
+    Eigen<T, M> eg;
+    EigenAdj<T> ge;
+    T gw[M], w[M], gU1[M], gU2[M];
+#pragma unroll
+    for (int c = 0; c < M; ++c) w[c] = T(0);
+    if constexpr (PROJ) {
+      T U1[M], U2[M], dn[M];
+      lds(1, U1, dn);
+      lds(2, U2, dn);
+      eg.roe(U1, U2, k.gm1);
+      back_T(eg, gf, gw);
+#pragma unroll
+      for (int c = 0; c < M; ++c) gw[c] *= T(1.0 / 6.0);
+    } else {
+#pragma unroll
+      for (int c = 0; c < M; ++c) gw[c] = T(1.0 / 6.0) * gf[c];
+    }
+    // one phase: gx, gy to point s's sums, gU (if any) to its cell
+    auto add = [&](int s, const T* gx, const T* gy, const T* gU) __attribute__((always_inline)) {
+      const int px = sx + (d == 0 ? s : 0), py = sy + (d == 1 ? s : 0);
+      __syncthreads();
+      if (any && px >= 0 && px < TX && py >= 0 && py < TY) {
+        T* p = pool + py * TX + px;
+        T* u = accs + py * TX + px;
 #pragma unroll
         for (int c = 0; c < M; ++c) {
-          put(c, any ? gU[c] : T(0));
-          put(M + c, any ? gDn[c] : T(0));
-          if constexpr (DIM == 2) put(2 * M + c, any ? gDt[c] : T(0));
+          p[c * AS] += gx[c];
+          p[(M + c) * AS] += gy[c];
+          if (gU) u[cs(c) * AS] += gU[c];
         }
       }
-      __syncthreads();
-      if (owner) {
-        if (mode == EMIT_ADD_U) {
-#pragma unroll
-          for (int c = 0; c < M; ++c) acc[(c) * AS] += col(c, qo - 1) + col(M + c, qo - 2);
-        } else {
-#pragma unroll
-          for (int f = 0; f < NF; ++f) acc[(f) * AS] += col(f, qo - s);
-        }
-      }
-      __syncthreads();
     };
-    interface_vjp<T, PHYS, M, DIM == 2>(ld, T(a.alpha[0]), hx, idx, k.ax, k, gf, ghc, gxc, emit);
-  }
-
+    T gxa[M], gya[M], gxo[M], gyo[M], gxb[M], gyb[M], pF[M], pA[M];
+    side_vjp<T, PHYS, M, PROJ>(lds, true, alpha, an, k, eg, gw, gf, w, ge, gxa, gya, gxo, gyo, gxb, gyb);
+    add(0, gxa, gya, nullptr);
+    add(1, gxo, gyo, nullptr);
+    add(2, gxb, gyb, nullptr);
+    __syncthreads();
+    if (owner) {
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        pF[c] = pool[c * AS + tid], pA[c] = pool[(M + c) * AS + tid];
+        pool[c * AS + tid] = pool[(M + c) * AS + tid] = T(0);
+      }
+    }
+    side_vjp<T, PHYS, M, PROJ>(lds, false, alpha, an, k, eg, gw, gf, w, ge, gxa, gya, gxo, gyo, gxb, gyb);
+    if constexpr (PROJ) {
+      // the reconstructed fields' way back, then the Roe average
+#pragma unroll
+      for (int c = 0; c < M; ++c) w[c] *= T(1.0 / 6.0), gU1[c] = gU2[c] = T(0);
+      back_eigen_adj(eg, w, gf, ge);
+      T U1[M], U2[M], dn[M];
+      lds(1, U1, dn);
+      lds(2, U2, dn);
+      roe_vjp<T, M>(U1, U2, k.gm1, ge, gU1, gU2);
+    }
+    add(3, gxa, gya, nullptr);
+    add(2, gxo, gyo, PROJ ? gU2 : nullptr);
+    add(1, gxb, gyb, PROJ ? gU1 : nullptr);
+    __syncthreads();
+    if (owner) {
+      // through the point fluxes: x+- = F +- alpha U, y+- = A +- alpha Dn
+      T gF[M], gA[M], gU[M], gN[M];
+      bool some = false;
+#pragma unroll
+      for (int c = 0; c < M; ++c) {
+        const T mF = pool[c * AS + tid], mA = pool[(M + c) * AS + tid];
+        some = some || pF[c] != T(0) || pA[c] != T(0) || mF != T(0) || mA != T(0);
+        gF[c] = pF[c] + mF, gU[c] = alpha * (pF[c] - mF);
+        gA[c] = pA[c] + mA, gN[c] = alpha * (pA[c] - mA);
+      }
+      if (some) {
+        T U[M], Dn[M];
+        ld(own, U, Dn);
+        point_fluxes_vjp<T, PHYS, M, false>(U, Dn, Dn, k, an, gF, gA, nullptr, gU, gN, nullptr);
+        add_cell(gU, gN);
+      }
+    }
+  };
+  direction(std::integral_constant<int, 0>{});
   if constexpr (DIM == 2) {
-    const T idy = T(1.0 / a.dy), hy = T(a.dy);
-    // ---- y-interfaces J (between rows J and J+1) that touch the tile ----
-    const int q = tid < NIY ? tid : NIY - 1;
-    const int jj = q / TX, cc = q - jj * TX;
-    const int i = rx0 + cc, J = ry0 - 2 + jj;
-    T gf[M], gh[M], gx[M];
-    bool any = false;
-    const bool live = tid < NIY && i >= 0 && i < nx && J >= -1 && J <= ny - 1;
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-      const int cs = (PHYS == PH_EULER && (c == 1 || c == 2)) ? 3 - c : c;
-      gf[c] = live ? cr * (xl(cs, i, J + 1) - xl(cs, i, J)) * idy : T(0);
-      gh[c] = live ? cr * (xl(2 * M + cs, i, J + 1) - xl(2 * M + cs, i, J)) * idy : T(0);  // theta-hat
-      gx[c] = live ? cr * (xl(M + cs, i, J + 1) - xl(M + cs, i, J)) * idy : T(0);          // xi-hat
-      any = any || gf[c] != T(0) || gh[c] != T(0) || gx[c] != T(0);
-    }
-    __syncthreads();  // the x pass's last readers of gin are done
-#pragma unroll
-    for (int c = 0; c < M; ++c) {
-      gin[c * NT + tid] = gh[c];
-      gin[(M + c) * NT + tid] = gx[c];
-    }
-    const Col<T> ghc{gin + tid, NT}, gxc{gin + M * NT + tid, NT};
-    const T* colp = cell(i, J - 1);
-    auto ld = [&](int s, T* U, T* Dn, T* Dt) {
-      const T* p = colp + s * (W * NF);
-#pragma unroll
-      for (int c = 0; c < M; ++c) {
-        // normal frame: swap the two momenta; Dn = U_y, Dt = U_x
-        const int cs = (PHYS == PH_EULER && (c == 1 || c == 2)) ? 3 - c : c;
-        U[c] = p[cs];
-        Dn[c] = p[2 * M + cs];
-        Dt[c] = p[M + cs];
-      }
-    };
-    // entry (lx, ly) is point s of interface jj = ly + 3 - s in its column
-    const int qo = (ly + 3) * TX + lx;
-    auto emit = [&](int s, int mode, const T* gU, const T* gDn, const T* gDt) {
-      if (mode == EMIT_ADD_U) {
-#pragma unroll
-        for (int c = 0; c < M; ++c) {
-          const int cs = (PHYS == PH_EULER && (c == 1 || c == 2)) ? 3 - c : c;
-          put((s == 1 ? 0 : M) + cs, any ? gU[c] : T(0));
-        }
-        if (s == 1) return;
-      } else {
-#pragma unroll
-        for (int c = 0; c < M; ++c) {
-          const int cs = (PHYS == PH_EULER && (c == 1 || c == 2)) ? 3 - c : c;
-          put(cs, any ? gU[c] : T(0));
-          put(2 * M + cs, any ? gDn[c] : T(0));
-          put(M + cs, any ? gDt[c] : T(0));
-        }
-      }
-      __syncthreads();
-      if (owner) {
-        if (mode == EMIT_ADD_U) {
-#pragma unroll
-          for (int c = 0; c < M; ++c) acc[(c) * AS] += col(c, qo - TX) + col(M + c, qo - 2 * TX);
-        } else {
-#pragma unroll
-          for (int f = 0; f < NF; ++f) acc[(f) * AS] += col(f, qo - s * TX);
-        }
-      }
-      __syncthreads();
-    };
-    interface_vjp<T, PHYS, M, true>(ld, T(a.alpha[1]), hy, idy, k.ay, k, gf, ghc, gxc, emit);
+    __syncthreads();  // the pool's last reads are done
+    direction(std::integral_constant<int, 1>{});
   }
 
   // ---- limiter: U_x along x (and U_y along y) of cells near the tile ----
-  // contributions of the limiter at cell C, component c: U at C-1, C, C+1
-  // (handed over together), then the derivative at C-1 and C+1
+  // the limiter at cell C reads U at C-1, C, C+1 and the derivative at C-1, C+1
+  auto limiter = [&](auto dir) __attribute__((always_inline)) {
+    constexpr int d = decltype(dir)::value;
+    constexpr int NL = d == 0 ? NLX : NLY;
+    constexpr int ST = d == 0 ? NF : W * NF;
+    constexpr int ON = (1 + d) * M;
+    const T ihn = d == 0 ? idx : idy;
+    const int q = tid < NL ? tid : NL - 1;
+    const int qr = d == 0 ? q / (TX + 2) : q / TX;
+    const int qc = d == 0 ? q - qr * (TX + 2) : q - qr * TX;
+    const int sx = d == 0 ? qc - 1 : qc, sy = d == 0 ? qr : qr - 1;  // C in the tile
+    const int ci = rx0 + sx, cj = ry0 + sy;
+    const bool live = tid < NL && cj >= 0 && cj < ny && ci >= 0 && ci < nx;
+    const T* p = live ? cell(ci, cj) : sm + ST;
+    T gm[M], g0[M], gp[M], gvm[M], gvp[M], mu[M];
+    bool any = false;
+#pragma unroll
+    for (int c = 0; c < M; ++c) {
+      mu[c] = live ? cl * gld(a.XM + (d * M + c) * fs + (long long)cj * nx + ci) * ihn : T(0);
+      any = any || mu[c] != T(0);
+      gm[c] = g0[c] = gp[c] = gvm[c] = gvp[c] = T(0);
+    }
+    const bool charlim = EU && (MODE == MODE_CHAR_LIM || (MODE == MODE_COMP && k.limiter_char));
+    auto cs = [&](int c) { return (EU && charlim && d == 1 && (c == 1 || c == 2)) ? 3 - c : c; };
+    if (any) {
+      auto args = [&](int f, T& d1, T& d2, T& vs, T& vd) __attribute__((always_inline)) {
+        d1 = p[f] - p[f - ST], d2 = p[f + ST] - p[f];
+        const T vm = p[ON + f - ST], vp = p[ON + f + ST];
+        vs = vm + vp, vd = vm - vp;
+      };
+      if (!charlim) {
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+          T d1, d2, vs, vd, g1, g2, gs, gd;
+          args(c, d1, d2, vs, vd);
+          limit_blend_vjp(d1, d2, vs, vd, k.lw.g1, k.lw.g2, k.lw.eps, mu[c], g1, g2, gs, gd);
+          gm[c] = -g1, g0[c] = g1 - g2, gp[c] = g2, gvm[c] = gs + gd, gvp[c] = gs - gd;
+        }
+      } else if constexpr (EU && MODE != MODE_CHAR) {
+        // characteristic variant, in the normal frame (the momenta swap places for y)
+        T u0[M], d1[M], d2[M], vs[M], vd[M], go[M], gu[M], g1[M], g2[M], gs[M], gd[M];
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+          const int f = d == 1 && (c == 1 || c == 2) ? 3 - c : c;
+          u0[c] = p[f];
+          go[c] = mu[f];
+          args(f, d1[c], d2[c], vs[c], vd[c]);
+        }
+        limit_char_d_vjp<T, M>(u0, d1, d2, vs, vd, k.lw.g1, k.lw.g2, k.lw.eps, k.gm1, go, gu, g1, g2,
+                               gs, gd);
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+          const int f = d == 1 && (c == 1 || c == 2) ? 3 - c : c;
+          gm[f] = -g1[c], g0[f] = gu[c] + (g1[c] - g2[c]), gp[f] = g2[c];
+          gvm[f] = gs[c] + gd[c], gvp[f] = gs[c] - gd[c];
+        }
+      }
+    }
+    // phase: gu to U and gv (if any) to the derivative of cell C + s
+    auto add = [&](int s, const T* gu, const T* gv) __attribute__((always_inline)) {
+      const int px = sx + (d == 0 ? s : 0), py = sy + (d == 1 ? s : 0);
+      __syncthreads();
+      if (any && px >= 0 && px < TX && py >= 0 && py < TY) {
+        T* u = accs + py * TX + px;
+#pragma unroll
+        for (int c = 0; c < M; ++c) {
+          u[c * AS] += gu[c];
+          if (gv) u[(ON + c) * AS] += gv[c];
+        }
+      }
+    };
+    add(-1, gm, gvm);
+    add(0, g0, nullptr);
+    add(1, gp, gvp);
+  };
   if (a.XM) {
-    {
-      const int q = tid < NLX ? tid : NLX - 1;
-      const int r = q / (TX + 2), ii = q - r * (TX + 2);
-      const int j = ry0 + r, C = rx0 - 1 + ii;
-      const bool live = tid < NLX && j >= 0 && j < ny && C >= 0 && C < nx;
-      const T* p = live ? cell(C, j) : sm + NF;
-      T g[5][M];
-#pragma unroll
-      for (int c = 0; c < M; ++c)
-#pragma unroll
-        for (int s5 = 0; s5 < 5; ++s5) g[s5][c] = T(0);
-      if constexpr (CL && PHYS == PH_EULER) {
-        T mu[M];
-        bool any = false;
-#pragma unroll
-        for (int c = 0; c < M; ++c) {
-          mu[c] = live ? cl * a.XM[c * fs + (long long)j * nx + C] : T(0);
-          any = any || mu[c] != T(0);
-        }
-        if (any) {
-          T um[M], u0[M], up[M], vm[M], vp[M];
-#pragma unroll
-          for (int c = 0; c < M; ++c) {
-            um[c] = p[-NF + c], u0[c] = p[c], up[c] = p[NF + c];
-            vm[c] = p[-NF + M + c], vp[c] = p[NF + M + c];
-          }
-          limit_char_vjp<T, M>(um, u0, up, vm, vp, hx, idx, k.lw, k.gm1, mu, g[0], g[1], g[2],
-                               g[3], g[4]);
-        }
-      } else {
-#pragma unroll
-        for (int c = 0; c < M; ++c) {
-          const T mu = live ? cl * a.XM[c * fs + (long long)j * nx + C] : T(0);
-          if (mu != T(0))
-            limit1_vjp(p[-NF + c], p[c], p[NF + c], p[-NF + M + c], p[NF + M + c], hx, idx, k.lw,
-                       mu, g[0][c], g[1][c], g[2][c], g[3][c], g[4][c]);
-        }
-      }
-      // entry P = rx0 + lx: the limiter of cell C sits at ii = C - rx0 + 1
-      const int qb = ly * (TX + 2) + lx + 1;
-#pragma unroll
-      for (int c = 0; c < M; ++c) {
-        put(c, g[0][c]);
-        put(M + c, g[1][c]);
-        put(2 * M + c, g[2][c]);
-      }
-      __syncthreads();
-      if (owner) {
-#pragma unroll
-        for (int c = 0; c < M; ++c)
-          acc[(c) * AS] += col(c, qb + 1) + col(M + c, qb) + col(2 * M + c, qb - 1);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int c = 0; c < M; ++c) {
-        put(c, g[3][c]);
-        put(M + c, g[4][c]);
-      }
-      __syncthreads();
-      if (owner) {
-#pragma unroll
-        for (int c = 0; c < M; ++c) acc[(M + c) * AS] += col(c, qb + 1) + col(M + c, qb - 1);
-      }
-      __syncthreads();
-    }
-    if constexpr (DIM == 2) {
-      const T idy = T(1.0 / a.dy), hy = T(a.dy);
-      const int q = tid < NLY ? tid : NLY - 1;
-      const int jj = q / TX, cc = q - jj * TX;
-      const int i = rx0 + cc, C = ry0 - 1 + jj;
-      const bool live = tid < NLY && i >= 0 && i < nx && C >= 0 && C < ny;
-      const T* p = live ? cell(i, C) : sm + W * NF;
-      constexpr int S = W * NF;
-      T g[5][M];
-#pragma unroll
-      for (int c = 0; c < M; ++c)
-#pragma unroll
-        for (int s5 = 0; s5 < 5; ++s5) g[s5][c] = T(0);
-      if constexpr (CL && PHYS == PH_EULER) {
-        // normal frame: the two momenta swap places (as in the forward); the
-        // gradients come back in that frame and are swapped on hand-over
-        T mu[M];
-        bool any = false;
-#pragma unroll
-        for (int c = 0; c < M; ++c) {
-          const int qc = (c == 1) ? 2 : (c == 2) ? 1 : c;
-          mu[c] = live ? cl * a.XM[(M + qc) * fs + (long long)C * nx + i] : T(0);
-          any = any || mu[c] != T(0);
-        }
-        if (any) {
-          T um[M], u0[M], up[M], vm[M], vp[M];
-#pragma unroll
-          for (int c = 0; c < M; ++c) {
-            const int qc = (c == 1) ? 2 : (c == 2) ? 1 : c;
-            um[c] = p[-S + qc], u0[c] = p[qc], up[c] = p[S + qc];
-            vm[c] = p[-S + 2 * M + qc], vp[c] = p[S + 2 * M + qc];
-          }
-          limit_char_vjp<T, M>(um, u0, up, vm, vp, hy, idy, k.lw, k.gm1, mu, g[0], g[1], g[2],
-                               g[3], g[4]);
-        }
-      } else {
-#pragma unroll
-        for (int c = 0; c < M; ++c) {
-          const T mu = live ? cl * a.XM[(M + c) * fs + (long long)C * nx + i] : T(0);
-          if (mu != T(0))
-            limit1_vjp(p[-S + c], p[c], p[S + c], p[-S + 2 * M + c], p[S + 2 * M + c], hy, idy,
-                       k.lw, mu, g[0][c], g[1][c], g[2][c], g[3][c], g[4][c]);
-        }
-      }
-      auto fc = [&](int c) { return (CL && PHYS == PH_EULER) ? ((c == 1) ? 2 : (c == 2) ? 1 : c) : c; };
-      const int qb = (ly + 1) * TX + lx;  // jj of C = P
-#pragma unroll
-      for (int c = 0; c < M; ++c) {
-        put(fc(c), g[0][c]);
-        put(M + fc(c), g[1][c]);
-        put(2 * M + fc(c), g[2][c]);
-      }
-      __syncthreads();
-      if (owner) {
-#pragma unroll
-        for (int c = 0; c < M; ++c)
-          acc[(c) * AS] += col(c, qb + TX) + col(M + c, qb) + col(2 * M + c, qb - TX);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int c = 0; c < M; ++c) {
-        put(fc(c), g[3][c]);
-        put(M + fc(c), g[4][c]);
-      }
-      __syncthreads();
-      if (owner) {
-#pragma unroll
-        for (int c = 0; c < M; ++c) acc[(2 * M + c) * AS] += col(c, qb + TX) + col(M + c, qb - TX);
-      }
-    }
+    limiter(std::integral_constant<int, 0>{});
+    if constexpr (DIM == 2) limiter(std::integral_constant<int, 1>{});
   }
+  __syncthreads();
   if (owner) {
     const int ex = btx * TX + lx, ey = bty * TY + ly;
     if (ex < a.nxe && ey < a.nye) {
@@ -1432,7 +1421,7 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
       const bool inner = i >= 2 && i < nx - 2 && (DIM == 1 || (j >= 2 && j < ny - 2));
       T v[NF];
 #pragma unroll
-      for (int f = 0; f < NF; ++f) v[f] = acc[f * AS];
+      for (int f = 0; f < NF; ++f) v[f] = staged(acc[f * AS], f, M, hx, hy);
       if (a.fused && inner) {
         fold_finish<T, NF>(a.fo, (long long)j * nx + i, v);
       } else {
@@ -2207,14 +2196,15 @@ struct RunAdj {
     a.fo = fo;
     constexpr int TX = AdjTile<DIM>::TX, TY = AdjTile<DIM>::TY, NT = AdjTile<DIM>::NT;
     const unsigned tiles = (unsigned)(((L.nxe + TX - 1) / TX) * ((L.nye + TY - 1) / TY));
-    if constexpr (PHYS == PH_EULER) {
-      if (char_limiter(p))
-        timed(s, [&] { k_adjoint<T, PHYS, DIM, TX, TY, NT, true><<<tiles, NT, 0, s>>>(a, make_consts<T>(p)); });
-      else
-        timed(s, [&] { k_adjoint<T, PHYS, DIM, TX, TY, NT, false><<<tiles, NT, 0, s>>>(a, make_consts<T>(p)); });
-    } else {
-      timed(s, [&] { k_adjoint<T, PHYS, DIM, TX, TY, NT, false><<<tiles, NT, 0, s>>>(a, make_consts<T>(p)); });
-    }
+    auto launch = [&](auto mode) {
+      timed(s, [&] {
+        k_adjoint<T, PHYS, DIM, TX, TY, NT, decltype(mode)::value><<<tiles, NT, 0, s>>>(a, make_consts<T>(p));
+      });
+    };
+    if constexpr (PHYS == PH_EULER)
+      with_mode(p, launch);
+    else
+      launch(std::integral_constant<int, MODE_COMP>{});
     if (a.fused) {
       const long long nb = (4ll * a.ny + 4ll * (a.nx - 4)) * fo.nf;
       k_fold_band<T><<<(unsigned)((nb + 255) / 256), 256, 0, s>>>(fo);

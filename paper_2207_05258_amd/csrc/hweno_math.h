@@ -241,11 +241,12 @@ HW_HD T hw_plus(T fm, T f0, T fp, T Hm, T H0, T Hp, const Weights<T>& w) {
   return mad(T(1.0 / 12.0), r, mad(T(0.5), H0, f0));
 }
 
-// HWENO limiter value v~_i (Section 2.2) from d1 = u_i - u_{i-1}, d2 = u_{i+1} - u_i,
-// Vs = h (v_{i-1} + v_{i+1}), Vd = h (v_{i-1} - v_{i+1}): h v~_i = (d1 + d2)/2 plus
-// the correction returned here.  Candidates (quartic q0, linear q1, q2), with
-// D = d1 + d2, lap = d2 - d1 and e = Vs - D: q0' = D/2 - e/4, q1' = D/2 - lap/2,
-// q2' = D/2 + lap/2.  The quartic's indicator from its coefficients a1..a4,
+// HWENO limiter (Section 2.2): h v~_i from d1 = u_i - u_{i-1}, d2 = u_{i+1} - u_i,
+// Vs = h (v_{i-1} + v_{i+1}), Vd = h (v_{i-1} - v_{i+1}).  Candidates (quartic q0,
+// linear q1, q2), with D = d1 + d2, lap = d2 - d1, e = Vs - D: 3/4 D - Vs/4, d1, d2,
+// combined whole: a part common to them, D/2, would carry a jump's rounding into
+// a limited value on its smooth side.  The quartic's indicator from its
+// coefficients a1..a4,
 //   (a1 + a3/4)^2 + 13/3 (a2 + 63/130 a4)^2 + 781/20 a3^2 + 1421461/2275 a4^2,
 // is a sum of squares of linear forms; the second and fourth are a quadratic
 // form of (Vd, lap), rotated so that one square is of lap alone.
@@ -253,23 +254,19 @@ template <typename T>
 HW_HD T limit_blend(T d1, T d2, T Vs, T Vd, const Blend<T>& w) {
   const T D = d1 + d2, lap = d2 - d1, e = Vs - D;
   const T x0 = mad(T(0.5), D, T(-3.0 / 16.0) * e);  // a1 + a3/4
+  const T a1 = mad(T(0.75), D, T(-0.25) * Vs);
   const T y = mad(T(12.554318802466193), lap, T(6.254843361443233) * Vd);
   const T c0 = mad(T(1.0813413108057222) * lap, lap,
                    mad(T(2.440625) * e, e, mad(y, y, mad(x0, x0, w.eps))));
-  const T r = blend_c<12>(c0, mad(d1, d1, w.eps), mad(d2, d2, w.eps), w,
-                          [=](T m, T s1, T s2, T f) {
-                            return mad(m, e, T(-2) * ((f * lap) * (s2 - s1)));
-                          });
-  return T(-0.25) * r;
+  return blend_c<12>(c0, mad(d1, d1, w.eps), mad(d2, d2, w.eps), w,
+                     [=](T m, T s1, T s2, T f) { return mad(m, a1, f * mad(s1, d1, s2 * d2)); });
 }
 
 // limited derivative from u_{i-1}, u_i, u_{i+1}, v_{i-1}, v_{i+1}; h = dx, ih = 1/dx
 template <typename T>
 HW_HD T limit1(T um, T u0, T up, T vm, T vp, T h, T ih, const Weights<T>& w) {
-  const T d1 = u0 - um, d2 = up - u0;
-  return ih * mad(T(0.5), d1 + d2,
-                  limit_blend(d1, d2, h * (vm + vp), h * (vm - vp),
-                              limit_blend_weights(w.g1, w.g2, w.eps)));
+  return ih * limit_blend(u0 - um, up - u0, h * (vm + vp), h * (vm - vp),
+                          limit_blend_weights(w.g1, w.g2, w.eps));
 }
 
 // ---------------------------------------------------------------------------
@@ -391,8 +388,7 @@ struct Eigen {
 };
 
 // Characteristic variant of the limiter, h times the limited derivative, from
-// the differences of limit_blend: the part (d1 + d2)/2 common to the candidates is
-// the same in every basis, so only the correction goes through the eigenvectors.
+// the differences of limit_blend.
 template <typename T, int M>
 HW_HD void limit_char_d(const T* u0, const T* d1, const T* d2, const T* Vs, const T* Vd,
                         const Blend<T>& w, T gm1, T* out) {
@@ -406,8 +402,6 @@ HW_HD void limit_char_d(const T* u0, const T* d1, const T* d2, const T* Vs, cons
 #pragma unroll
   for (int q = 0; q < M; ++q) z[q] = limit_blend(a[q], b[q], s[q], d[q], w);
   e.back(z, out);
-#pragma unroll
-  for (int q = 0; q < M; ++q) out[q] = mad(T(0.5), d1[q] + d2[q], out[q]);
 }
 
 // Characteristic variant of the limiter (a choice the paper leaves open for
