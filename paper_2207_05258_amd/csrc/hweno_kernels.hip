@@ -151,32 +151,63 @@ __device__ __forceinline__ unsigned long long dbits(double x) {
   return (unsigned long long)__double_as_longlong(x);
 }
 
-// workgroup reduction of two non-negative speeds (as bit patterns, so NaN
+// Maximum over a wave of non-negative values, on every lane; NaN wins.  Six DPP
+// moves within the vector unit: a chain of LDS permutes took a tenth of the
+// time of a small grid's stage.
+template <int C>
+__device__ __forceinline__ float dpp_shift(float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), C, 0xf, 0xf, false));
+}
+template <int C>
+__device__ __forceinline__ double dpp_shift(double x) {
+  return __hiloint2double(
+      __builtin_amdgcn_update_dpp(0, __double2hiint(x), C, 0xf, 0xf, false),
+      __builtin_amdgcn_update_dpp(0, __double2loint(x), C, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float last_lane(float x) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+__device__ __forceinline__ double last_lane(double x) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 63),
+                          __builtin_amdgcn_readlane(__double2loint(x), 63));
+}
+template <typename T>
+__device__ __forceinline__ T wave_max(T x) {
+  const bool nan = __builtin_amdgcn_ballot_w64(x != x) != 0;  // fmax drops NaN
+  // lanes n-1, n-2, n-4, n-8 of a row of 16, then the last lanes of rows 0 and 2
+  // to rows 1 and 3, and that of the lower half to the upper one; lanes without a
+  // source read 0
+  x = fmax(x, dpp_shift<0x111>(x));
+  x = fmax(x, dpp_shift<0x112>(x));
+  x = fmax(x, dpp_shift<0x114>(x));
+  x = fmax(x, dpp_shift<0x118>(x));
+  x = fmax(x, dpp_shift<0x142>(x));
+  x = fmax(x, dpp_shift<0x143>(x));
+  return nan ? T(__builtin_nan("")) : last_lane(x);
+}
+
+// workgroup reduction of two non-negative speeds (compared as bit patterns, so NaN
 // wins) and of status flags; thread 0 folds them into global memory.
-template <int NT>
-__device__ __forceinline__ void block_fold(double sx, double sy, uint32_t flags,
-                                           double* slot, unsigned long long* status,
-                                           bool do_speeds) {
+template <int NT, typename T>
+__device__ __forceinline__ void block_fold(T sx, T sy, uint32_t flags, double* slot,
+                                           unsigned long long* status, bool do_speeds) {
   __shared__ unsigned long long red[NT / 64][2];
   __shared__ uint32_t redf[NT / 64];
-  unsigned long long bx = dbits(sx), by = dbits(sy);
+  sx = wave_max(sx);
+  sy = wave_max(sy);
+  if (__builtin_amdgcn_ballot_w64(flags != 0)) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    unsigned long long ox = __shfl_xor(bx, off);
-    unsigned long long oy = __shfl_xor(by, off);
-    uint32_t of = __shfl_xor(flags, off);
-    bx = ox > bx ? ox : bx;
-    by = oy > by ? oy : by;
-    flags |= of;
+    for (int off = 32; off > 0; off >>= 1) flags |= __shfl_xor(flags, off);
   }
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   if (lane == 0) {
-    red[wv][0] = bx;
-    red[wv][1] = by;
+    red[wv][0] = dbits(double(sx));
+    red[wv][1] = dbits(double(sy));
     redf[wv] = flags;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
+    unsigned long long bx = red[0][0], by = red[0][1];
     for (int q = 1; q < NT / 64; ++q) {
       bx = red[q][0] > bx ? red[q][0] : bx;
       by = red[q][1] > by ? red[q][1] : by;
@@ -187,13 +218,15 @@ __device__ __forceinline__ void block_fold(double sx, double sy, uint32_t flags,
     // lower bound of the final maximum: a workgroup whose maximum does not
     // exceed it has nothing to add.  Once the first workgroups have folded
     // theirs, almost every later one skips its atomic, and tens of thousands
-    // of read-modify-writes no longer queue on one address.
+    // of read-modify-writes no longer queue on one address.  A few workgroups do
+    // not queue (about 15 ns each), and waiting for the read would cost them more.
     using gu64 = __attribute__((address_space(1))) unsigned long long;
     if (do_speeds) {
-      const unsigned long long cx =
-          __hip_atomic_load((gu64*)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const unsigned long long cy =
-          __hip_atomic_load((gu64*)slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      unsigned long long cx = 0, cy = 0;
+      if (gridDim.x > 64) {
+        cx = __hip_atomic_load((gu64*)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        cy = __hip_atomic_load((gu64*)slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       if (bx > cx) __hip_atomic_fetch_max((gu64*)slot, bx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (by > cy)
         __hip_atomic_fetch_max((gu64*)slot + 1, by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -245,11 +278,9 @@ struct BandIter {
 
 // time step of stage K and the speeds it splits with (uniform per grid)
 template <int DIM, int K>
-__device__ __forceinline__ bool stage_dt(const StageArgs<double>* unused, double* ctrl,
-                                         double dt_fixed, double t_end, double cfl, double dx,
+__device__ __forceinline__ bool stage_dt(double* ctrl, double dt_fixed, double t_end, double cfl, double dx,
                                          double dy, int replay, bool leader,
                                          unsigned long long* status, double& dt) {
-  (void)unused;
   if constexpr (K == 1) {
     if (replay) {
       dt = ctrl[6];
@@ -273,6 +304,23 @@ __device__ __forceinline__ bool stage_dt(const StageArgs<double>* unused, double
     dt = ctrl[6];
   }
   return dt > 0.0;
+}
+
+// what a stage (K > 0) or the right-hand side reads before it computes: the time
+// step and the speeds it splits with; false when the step is skipped
+template <int DIM, int K, typename T>
+__device__ __forceinline__ bool grid_begin(const StageArgs<T>& a, double& dt, double& alx,
+                                           double& aly) {
+  if constexpr (K == 0) {
+    alx = a.alpha[0];
+    aly = a.alpha[1];
+    return true;
+  } else {
+    alx = a.ctrl[2 * (K - 1)];
+    aly = a.ctrl[2 * (K - 1) + 1];
+    return stage_dt<DIM, K>(a.ctrl, a.dt_fixed, a.t_end, a.cfl, a.dx, a.dy, a.replay,
+                            blockIdx.x == 0 && threadIdx.x == 0, a.status, dt);
+  }
 }
 
 // the LDS rectangle of columns [c0, c1) and rows [r0, r1) holds solid cells
@@ -316,6 +364,8 @@ __device__ __forceinline__ void obstacle_mirror(const StageArgs<T>& a, const Edg
 // ---------------------------------------------------------------------------
 // One tile of one stage (K = 1, 2, 3) or of the right-hand side (K = 0).
 // NT threads; TX x TY cells (TX*TY <= NT); sm, fb: LDS staging buffers.
+// begin(dt, alx, aly): the time step and the speeds from the control block, false
+// when the step is skipped.
 // Returns this thread's contribution to the next stage's speeds.
 // ---------------------------------------------------------------------------
 // MODE: which fields the reconstruction and the limiter of the Euler equations
@@ -329,10 +379,10 @@ enum {
   MODE_COMP = 2        // reconstruction component by component, either limiter
 };
 
-template <typename T, int PHYS, int DIM, int K, int TX, int TY, int NT, int MODE, bool EDG = false>
+template <typename T, int PHYS, int DIM, int K, int TX, int TY, int NT, int MODE, bool EDG = false, typename Begin>
 __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T>& k,
-                                           int tile_x, int tile_y, double dt, double alx,
-                                           double aly, T* __restrict__ sm, T* __restrict__ fb,
+                                           int tile_x, int tile_y, const Begin& begin,
+                                           T* __restrict__ sm, T* __restrict__ fb,
                                            T& sx, T& sy, uint32_t& flags,
                                            const EdgeArgs* e = nullptr) {
   constexpr int M = Comps<PHYS, DIM>::M;
@@ -352,28 +402,49 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
   const T hx = T(a.dx), hy = T(a.dy);
 
   // ---- stage the tile and its halo in LDS ----
-  // All rounds' loads are issued before the first LDS write.
+  // All rounds' loads are issued before the first LDS write, and before the control
+  // block is waited for.  Tiles whose halo lies inside the grid need no boundary
+  // map: a uniform base and one 32-bit offset per lane (nx <= 2^24 keeps it
+  // in range) serve every field.
   constexpr int NS = (W * HR + NT - 1) / NT;
   T v[NS][NF];
+  const bool inner = i0 >= 2 && i0 - 2 + W <= nx && (DIM == 1 || (j0 >= HY && j0 - HY + HR <= ny)) &&
+                     (DIM == 1 || nx <= (1 << 24));
+  if (inner) {
+    const T* src = a.in + ((long long)(j0 - HY) * nx + (i0 - 2));
 #pragma unroll
-  for (int r = 0; r < NS; ++r) {
-    const int q = tid + r * NT;
-    if (q < W * HR) {
-      const int lr = q / W, lc = q - lr * W;
-      const int ii = i0 - 2 + lc, jj = j0 - HY + lr;
-      int gi, gj;
-      if constexpr (EDG) {
-        gi = map_edge(ii, nx, a.bc_x, e->mirror[0], e->mirror[1]);
-        gj = map_edge(jj, ny, a.bc_y, e->mirror[2], e->mirror[3]);
-      } else {
-        gi = map_index2(ii, nx, a.bc_x);
-        gj = (DIM == 2) ? map_index2(jj, ny, a.bc_y) : 0;
+    for (int r = 0; r < NS; ++r) {
+      const int q = tid + r * NT;
+      if (q < W * HR) {
+        const unsigned lr = (unsigned)q / W, lc = (unsigned)q - lr * W;
+        const unsigned o = lr * (unsigned)nx + lc;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[r][f] = gld(src + f * fs + o);
       }
-      const long long g = (long long)gj * nx + gi;
+    }
+  } else {
 #pragma unroll
-      for (int f = 0; f < NF; ++f) v[r][f] = gld(a.in + f * fs + g);
+    for (int r = 0; r < NS; ++r) {
+      const int q = tid + r * NT;
+      if (q < W * HR) {
+        const int lr = q / W, lc = q - lr * W;
+        const int ii = i0 - 2 + lc, jj = j0 - HY + lr;
+        int gi, gj;
+        if constexpr (EDG) {
+          gi = map_edge(ii, nx, a.bc_x, e->mirror[0], e->mirror[1]);
+          gj = map_edge(jj, ny, a.bc_y, e->mirror[2], e->mirror[3]);
+        } else {
+          gi = map_index2(ii, nx, a.bc_x);
+          gj = (DIM == 2) ? map_index2(jj, ny, a.bc_y) : 0;
+        }
+        const long long g = (long long)gj * nx + gi;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[r][f] = gld(a.in + f * fs + g);
+      }
     }
   }
+  double dt = 0.0, alx, aly;
+  if (!begin(dt, alx, aly)) return;  // the step is skipped (uniform over the workgroup)
 #pragma unroll
   for (int r = 0; r < NS; ++r) {
     const int q = tid + r * NT;
@@ -676,28 +747,21 @@ __global__ __launch_bounds__(NT, (StageOcc<T, K>::WAVES)) void k_stage(StageArgs
   __shared__ T sm[NF * (TY + 2 * HY) * (TX + 4)];
   __shared__ T fb[NQ * M * (TY + 1) * (TX + 1)];
 
-  double dt = 0.0, alx, aly;
-  if constexpr (K == 0) {
-    alx = a.alpha[0];
-    aly = a.alpha[1];
-  } else {
-    alx = a.ctrl[2 * (K - 1)];
-    aly = a.ctrl[2 * (K - 1) + 1];
-    if (!stage_dt<DIM, K>(nullptr, a.ctrl, a.dt_fixed, a.t_end, a.cfl, a.dx, a.dy, a.replay,
-                          blockIdx.x == 0 && threadIdx.x == 0, a.status, dt))
-      return;  // uniform over the grid: the step is skipped
-  }
   const int ntx = (a.nx + TX - 1) / TX;
   const int t = xcd_band(blockIdx.x, gridDim.x);
   const int tile_y = t / ntx, tile_x = t - tile_y * ntx;
   T sx = T(0), sy = T(0);
   uint32_t flags = 0;
-  stage_tile<T, PHYS, DIM, K, TX, TY, NT, MODE>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb, sx, sy,
-                                              flags);
+  bool ran = true;
+  const auto begin = [&](double& dt, double& alx, double& aly) {
+    return ran = grid_begin<DIM, K>(a, dt, alx, aly);
+  };
+  stage_tile<T, PHYS, DIM, K, TX, TY, NT, MODE>(a, k, tile_x, tile_y, begin, sm, fb, sx, sy, flags);
+  if (!ran) return;
   if constexpr (K > 0) {
     // speeds of the new stage state feed the next stage's splitting; after
     // stage 3 they are the next step's stage-1 speeds (multi-step calls)
-    block_fold<NT>(double(sx), double(sy), flags, a.ctrl + (K < 3 ? 2 * K : 10), a.status,
+    block_fold<NT>(sx, sy, flags, a.ctrl + (K < 3 ? 2 * K : 10), a.status,
                    !a.replay && (K < 3 || a.fold_next));
   }
 }
@@ -723,28 +787,22 @@ __global__ __launch_bounds__(NT, (EdgeOcc<T>::WAVES)) void k_stage_edges(StageAr
   __shared__ T sm[NF * (TY + 2 * HY) * (TX + 4)];
   __shared__ T fb[NQ * M * (TY + 1) * (TX + 1)];
 
-  double dt = 0.0, alx, aly;
-  if constexpr (K == 0) {
-    alx = a.alpha[0];
-    aly = a.alpha[1];
-  } else {
-    alx = a.ctrl[2 * (K - 1)];
-    aly = a.ctrl[2 * (K - 1) + 1];
-    if (!stage_dt<DIM, K>(nullptr, a.ctrl, a.dt_fixed, a.t_end, a.cfl, a.dx, a.dy, a.replay,
-                          blockIdx.x == 0 && threadIdx.x == 0, a.status, dt))
-      return;  // uniform over the grid: the step is skipped
-  }
   const int ntx = (a.nx + TX - 1) / TX;
   const int t = xcd_band(blockIdx.x, gridDim.x);
   const int tile_y = t / ntx, tile_x = t - tile_y * ntx;
   T sx = T(0), sy = T(0);
   uint32_t flags = 0;
-  stage_tile<T, PH_EULER, 2, K, TX, TY, NT, MODE, true>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb,
-                                                      sx, sy, flags, &e);
+  bool ran = true;
+  const auto begin = [&](double& dt, double& alx, double& aly) {
+    return ran = grid_begin<2, K>(a, dt, alx, aly);
+  };
+  stage_tile<T, PH_EULER, 2, K, TX, TY, NT, MODE, true>(a, k, tile_x, tile_y, begin, sm, fb, sx, sy,
+                                                        flags, &e);
+  if (!ran) return;
   if constexpr (K > 0) {
     // speeds of the new stage state feed the next stage's splitting; after
     // stage 3 they are the next step's stage-1 speeds (multi-step calls)
-    block_fold<NT>(double(sx), double(sy), flags, a.ctrl + (K < 3 ? 2 * K : 10), a.status,
+    block_fold<NT>(sx, sy, flags, a.ctrl + (K < 3 ? 2 * K : 10), a.status,
                    !a.replay && (K < 3 || a.fold_next));
   }
 }
@@ -801,19 +859,21 @@ __device__ __forceinline__ void batched_tile(const hweno_instance* __restrict__ 
   constexpr int TX = BatchTile<V>::TX, TY = BatchTile<V>::TY, NT = BatchTile<V>::NT;
   const hweno_instance& I = inst[tile_map[t]];
   StageArgs<T> a = instance_args<T, K>(I, cfl);
-  double dt;
-  if (!stage_dt<2, K>(nullptr, a.ctrl, a.dt_fixed, a.t_end, cfl, a.dx, a.dy, 0,
-                      t == I.tile_begin[V] && threadIdx.x == 0, a.status, dt))
-    return;  // this instance's step is skipped
-  const double alx = a.ctrl[2 * (K - 1)], aly = a.ctrl[2 * (K - 1) + 1];
+  const bool leader = t == I.tile_begin[V] && threadIdx.x == 0;
+  bool ran = true;
+  const auto begin = [&](double& dt, double& alx, double& aly) {
+    alx = a.ctrl[2 * (K - 1)];
+    aly = a.ctrl[2 * (K - 1) + 1];
+    return ran = stage_dt<2, K>(a.ctrl, a.dt_fixed, a.t_end, cfl, a.dx, a.dy, 0, leader, a.status, dt);
+  };
   const int lt = t - I.tile_begin[V];
   const int ntx = (I.nx + TX - 1) / TX;
   const int tile_y = lt / ntx, tile_x = lt - tile_y * ntx;
   T sx = T(0), sy = T(0);
   uint32_t flags = 0;
-  stage_tile<T, PH_EULER, 2, K, TX, TY, NT, MODE>(a, k, tile_x, tile_y, dt, alx, aly, sm, fb, sx,
-                                                sy, flags);
-  block_fold<NT>(double(sx), double(sy), flags, a.ctrl + 2 * K, a.status, K < 3);
+  stage_tile<T, PH_EULER, 2, K, TX, TY, NT, MODE>(a, k, tile_x, tile_y, begin, sm, fb, sx, sy, flags);
+  if (!ran) return;
+  block_fold<NT>(sx, sy, flags, a.ctrl + 2 * K, a.status, K < 3);
 }
 
 // ONE: exactly one tile per workgroup (grid = tile count, XCD-banded order).
@@ -860,7 +920,7 @@ __global__ __launch_bounds__(256) void k_alpha_batched(const hweno_instance* __r
     if (q != cur) {  // uniform over the workgroup
       if (cur >= 0) {
         double* ctrl = (double*)inst[cur].ws;
-        block_fold<256>(double(sx), double(sy), flags, ctrl, (unsigned long long*)(ctrl + 8), true);
+        block_fold<256>(sx, sy, flags, ctrl, (unsigned long long*)(ctrl + 8), true);
         __syncthreads();  // the fold's LDS slots are reused by the next fold
         sx = sy = T(0);
         flags = 0;
@@ -889,7 +949,7 @@ __global__ __launch_bounds__(256) void k_alpha_batched(const hweno_instance* __r
   }
   if (cur >= 0) {
     double* ctrl = (double*)inst[cur].ws;
-    block_fold<256>(double(sx), double(sy), flags, ctrl, (unsigned long long*)(ctrl + 8), true);
+    block_fold<256>(sx, sy, flags, ctrl, (unsigned long long*)(ctrl + 8), true);
   }
 }
 
@@ -1450,7 +1510,7 @@ __global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, long lon
     mx = (dbits(double(sx)) > dbits(double(mx))) ? sx : mx;
     my = (dbits(double(sy)) > dbits(double(my))) ? sy : my;
   }
-  block_fold<256>(double(mx), double(my), flags, alpha, status, true);
+  block_fold<256>(mx, my, flags, alpha, status, true);
 }
 
 // k_alpha over the fluid cells of a 2D Euler grid with an obstacle (solid
@@ -1473,7 +1533,7 @@ __global__ __launch_bounds__(256) void k_alpha_obstacle(const T* __restrict__ S,
     mx = (dbits(double(sx)) > dbits(double(mx))) ? sx : mx;
     my = (dbits(double(sy)) > dbits(double(my))) ? sy : my;
   }
-  block_fold<256>(double(mx), double(my), flags, alpha, status, true);
+  block_fold<256>(mx, my, flags, alpha, status, true);
 }
 
 // Start of a step: stage speeds and dt from the replay record, or speeds
