@@ -174,7 +174,8 @@ typedef struct {
 hweno_status hweno_validate(const hweno_problem* prob);
 
 /* Bytes of device workspace hweno_rk3_step needs for `prob`
- * (control block, two stage states and the limited base derivatives).
+ * (control block, two stage states, the limited base derivatives and 1 KiB of
+ * partial speeds).
  * Returns 0 for an invalid problem. */
 size_t hweno_workspace_bytes(const hweno_problem* prob);
 
@@ -230,7 +231,7 @@ hweno_status hweno_rk3_step(const hweno_problem* prob, void* state, void* ws,
  * step k+1 are folded by step k's third stage (which already evaluates every
  * new cell) instead of by a separate pass over the state: the results, the
  * control block and the tapes are bitwise those of n_steps single calls.
- * Uses control-block entries [10..11] as scratch.  tapes: device
+ * Control-block entries [10..11] are scratch.  tapes: device
  * double[n_steps][HWENO_CTRL_LEN] (one record per step, as `tape` of
  * hweno_rk3_step) or NULL.  n_steps >= 0. */
 hweno_status hweno_rk3_steps(const hweno_problem* prob, void* state, void* ws, size_t ws_bytes,

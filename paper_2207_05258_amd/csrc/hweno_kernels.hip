@@ -43,6 +43,7 @@ struct StageArgs {
   const T* st0;       // S^n (stages 2 and 3 read U^n, and all of S^n without limiter)
   T* base;            // limited derivatives of S^n (written by stage 1, read by 2, 3)
   double* ctrl;       // step control block (stages only)
+  double* fold;       // speed slots (stages only; see NSLOT)
   unsigned long long* status;  // status word, or NULL
   const double* alpha;  // speeds for K == 0
   int nx, ny, bc_x, bc_y;
@@ -50,7 +51,7 @@ struct StageArgs {
   double dx, dy;
   double dt_fixed, t_end, cfl;
   int replay;
-  int fold_next;      // stage 3 folds the new state's speeds into ctrl[10..11]
+  int fold_next;      // stage 3 folds the new state's speeds for the next step
 };
 
 __device__ __forceinline__ int map_index(int i, int n, int bc) {
@@ -186,6 +187,54 @@ __device__ __forceinline__ T wave_max(T x) {
   return nan ? T(__builtin_nan("")) : last_lane(x);
 }
 
+// The speeds of a grid are maxima over all its workgroups.  On one address their
+// atomics queue, about 15 ns each: when the workgroups of a small grid finish
+// together that was a third of a 240 x 240 step.  So the workgroups of a grid fold
+// into NSLOT slots, one 128-byte line each, picked by blockIdx.x, and whoever needs
+// the speeds takes the maximum over the slots.  Line s holds, at
+// fold[s * SLOT_LEN + 2 q + direction], the speeds of the input of stage q + 1, and
+// for q = 3 those of the next step's first stage.
+// SLOT_FEW workgroups or fewer do not queue long enough to pay for reading several
+// lines (eight steps of 60 x 60, 16 workgroups: 288 us on one slot, 296 on eight; 160
+// x 120, 80 workgroups: 337 and 298): they use slot 0 alone.
+constexpr int NSLOT = 8, SLOT_LEN = 16, SLOT_FEW = 48;
+
+__device__ __forceinline__ int my_slot(int workgroups) {
+  return workgroups > SLOT_FEW ? (int)(blockIdx.x & (NSLOT - 1)) * SLOT_LEN : 0;
+}
+
+// The maxima over the slots, in two ways; NaN wins.  By lanes (0..7 the x-speeds, 8..15
+// the y-speeds), loaded before anything else so that nothing waits behind the halo
+// loads: the shorter wait, for workgroups that all start at once.
+__device__ __forceinline__ double slot_load(const double* fold, int q) {
+  const int lane = threadIdx.x & 63;
+  return lane < 2 * NSLOT ? gld(fold + (lane & (NSLOT - 1)) * SLOT_LEN + 2 * q + lane / NSLOT) : 0.0;
+}
+__device__ __forceinline__ void slot_max(double x, double& ax, double& ay) {
+  const unsigned long long nan = __builtin_amdgcn_ballot_w64(x != x);
+  x = fmax(x, dpp_shift<0x111>(x));  // lanes n-1, n-2, n-4 of the row
+  x = fmax(x, dpp_shift<0x112>(x));
+  x = fmax(x, dpp_shift<0x114>(x));
+  const double q_nan = __builtin_nan("");
+  ax = nan & 0xff ? q_nan : __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 7),
+                                             __builtin_amdgcn_readlane(__double2loint(x), 7));
+  ay = nan & 0xff00 ? q_nan : __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), 15),
+                                               __builtin_amdgcn_readlane(__double2loint(x), 15));
+}
+// By scalar loads, which later workgroups find in the scalar cache: nothing queues
+// with the halo loads (FP32, 2047 x 1531, four steps: 2.42 ms, by lanes 2.59 ms).
+__device__ __forceinline__ void slot_max_scalar(const double* fold, int q, double& ax, double& ay) {
+  double x = fold[2 * q], y = fold[2 * q + 1], sx = x, sy = y;
+#pragma unroll
+  for (int s = 1; s < NSLOT; ++s) {
+    const double u = fold[s * SLOT_LEN + 2 * q], v = fold[s * SLOT_LEN + 2 * q + 1];
+    x = fmax(x, u), y = fmax(y, v);
+    sx += u, sy += v;  // NaN, which fmax drops, stays in the sums
+  }
+  ax = sx != sx ? sx : x;
+  ay = sy != sy ? sy : y;
+}
+
 // workgroup reduction of two non-negative speeds (compared as bit patterns, so NaN
 // wins) and of status flags; thread 0 folds them into global memory.
 template <int NT, typename T>
@@ -219,11 +268,11 @@ __device__ __forceinline__ void block_fold(T sx, T sy, uint32_t flags, double* s
     // exceed it has nothing to add.  Once the first workgroups have folded
     // theirs, almost every later one skips its atomic, and tens of thousands
     // of read-modify-writes no longer queue on one address.  A few workgroups do
-    // not queue (about 15 ns each), and waiting for the read would cost them more.
+    // not queue for long, and waiting for the read would cost them more.
     using gu64 = __attribute__((address_space(1))) unsigned long long;
     if (do_speeds) {
       unsigned long long cx = 0, cy = 0;
-      if (gridDim.x > 64) {
+      if (gridDim.x > 512) {
         cx = __hip_atomic_load((gu64*)slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         cy = __hip_atomic_load((gu64*)slot + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
@@ -293,41 +342,85 @@ __device__ __forceinline__ double step_dt(double alx, double aly, double dt_fixe
   return (!(dt > 0.0) || !isfinite(dt)) ? 0.0 : dt;
 }
 
-// time step of stage K (uniform per grid); false when the step is skipped
+// time step of stage K (uniform per grid), stage 1's from the speeds alx, aly; false
+// when the step is skipped.  last, t: the control block's time step and time.
 template <int DIM, int K>
-__device__ __forceinline__ bool stage_dt(double* ctrl, double dt_fixed, double t_end, double cfl, double dx,
+__device__ __forceinline__ bool stage_dt(double* ctrl, double last, double t, double alx, double aly,
+                                         double dt_fixed, double t_end, double cfl, double dx,
                                          double dy, int replay, bool leader,
                                          unsigned long long* status, double& dt) {
-  if constexpr (K == 1) {
-    if (replay) {
-      dt = ctrl[6];
-    } else {
-      dt = step_dt<DIM>(ctrl[0], ctrl[1], dt_fixed, t_end, ctrl[7], cfl, dx, dy);
-      if (leader) {
-        ctrl[6] = dt;
-        if (dt == 0.0) atomicOr(status, (unsigned long long)HWENO_ST_SKIPPED);
-      }
+  if (K == 1 && !replay) {
+    dt = step_dt<DIM>(alx, aly, dt_fixed, t_end, t, cfl, dx, dy);
+    if (leader) {
+      ctrl[6] = dt;
+      if (dt == 0.0) atomicOr(status, (unsigned long long)HWENO_ST_SKIPPED);
     }
   } else {
-    dt = ctrl[6];
+    dt = last;
   }
   return dt > 0.0;
 }
 
+// Workgroups up to which the slots are read by lanes: what the chip holds at once
+// (two FP64 or four FP32 per compute unit).  Eight steps, by lanes and by scalar
+// loads: FP64 480 workgroups 454 and 457 us, 552 workgroups 610 and 601 us; FP32 552
+// workgroups 431 and 438 us, 1120 workgroups 631 and 625 us.
+template <typename T>
+__device__ __forceinline__ constexpr int slot_lanes() {
+  return sizeof(T) == 4 ? 1024 : 512;
+}
+
+// What a stage reads of the control block and the slots, before anything else and in
+// one go: read where each value is used, they wait one after the other (0.25 us a
+// stage).
+struct Early {
+  double lanes;     // slot_load's
+  double f0, f1;    // slot 0
+  double dt, time;  // ctrl[6], ctrl[7]
+};
+template <typename T, int K>
+__device__ __forceinline__ Early read_early(const StageArgs<T>& a) {
+  Early r = {0.0, 0.0, 0.0, 0.0, 0.0};
+  if constexpr (K > 0) {
+    const int n = (int)gridDim.x;
+    r.dt = a.ctrl[6], r.time = a.ctrl[7];
+    r.f0 = a.fold[2 * (K - 1)], r.f1 = a.fold[2 * (K - 1) + 1];
+    if (n > SLOT_FEW && n <= slot_lanes<T>()) r.lanes = slot_load(a.fold, K - 1);
+  }
+  return r;
+}
+
 // what a stage (K > 0) or the right-hand side reads before it computes: the time
-// step and the speeds it splits with; false when the step is skipped
+// step and the speeds it splits with (early: read_early's); false when the step is skipped
 template <int DIM, int K, typename T>
-__device__ __forceinline__ bool grid_begin(const StageArgs<T>& a, double& dt, double& alx,
-                                           double& aly) {
+__device__ __forceinline__ bool grid_begin(const StageArgs<T>& a, const Early& early, double& dt,
+                                           double& alx, double& aly) {
   if constexpr (K == 0) {
     alx = a.alpha[0];
     aly = a.alpha[1];
     return true;
   } else {
-    alx = a.ctrl[2 * (K - 1)];
-    aly = a.ctrl[2 * (K - 1) + 1];
-    return stage_dt<DIM, K>(a.ctrl, a.dt_fixed, a.t_end, a.cfl, a.dx, a.dy, a.replay,
-                            blockIdx.x == 0 && threadIdx.x == 0, a.status, dt);
+    const bool leader = blockIdx.x == 0 && threadIdx.x == 0;
+    if (a.replay) {
+      alx = a.ctrl[2 * (K - 1)];
+      aly = a.ctrl[2 * (K - 1) + 1];
+    } else {
+      const int n = (int)gridDim.x;
+      if (n <= SLOT_FEW)
+        alx = early.f0, aly = early.f1;
+      else if (n <= slot_lanes<T>())
+        slot_max(early.lanes, alx, aly);
+      else
+        slot_max_scalar(a.fold, K - 1, alx, aly);
+    }
+    const bool go = stage_dt<DIM, K>(a.ctrl, early.dt, early.time, alx, aly, a.dt_fixed, a.t_end,
+                                     a.cfl, a.dx, a.dy, a.replay, leader, a.status, dt);
+    // a skipped step leaves the speeds of its later stages at zero
+    if (!a.replay && leader && (K == 1 || go)) {
+      a.ctrl[2 * (K - 1)] = alx;
+      a.ctrl[2 * (K - 1) + 1] = aly;
+    }
+    return go;
   }
 }
 
@@ -761,15 +854,16 @@ __global__ __launch_bounds__(NT, (StageOcc<T, K>::WAVES)) void k_stage(StageArgs
   T sx = T(0), sy = T(0);
   uint32_t flags = 0;
   bool ran = true;
+  const Early early = read_early<T, K>(a);
   const auto begin = [&](double& dt, double& alx, double& aly) {
-    return ran = grid_begin<DIM, K>(a, dt, alx, aly);
+    return ran = grid_begin<DIM, K>(a, early, dt, alx, aly);
   };
   stage_tile<T, PHYS, DIM, K, TX, TY, NT, MODE>(a, k, tile_x, tile_y, begin, sm, fb, sx, sy, flags);
   if (!ran) return;
   if constexpr (K > 0) {
     // speeds of the new stage state feed the next stage's splitting; after
     // stage 3 they are the next step's stage-1 speeds (multi-step calls)
-    block_fold<NT>(sx, sy, flags, a.ctrl + (K < 3 ? 2 * K : 10), a.status,
+    block_fold<NT>(sx, sy, flags, a.fold + my_slot((int)gridDim.x) + 2 * K, a.status,
                    !a.replay && (K < 3 || a.fold_next));
   }
 }
@@ -801,8 +895,9 @@ __global__ __launch_bounds__(NT, (EdgeOcc<T>::WAVES)) void k_stage_edges(StageAr
   T sx = T(0), sy = T(0);
   uint32_t flags = 0;
   bool ran = true;
+  const Early early = read_early<T, K>(a);
   const auto begin = [&](double& dt, double& alx, double& aly) {
-    return ran = grid_begin<2, K>(a, dt, alx, aly);
+    return ran = grid_begin<2, K>(a, early, dt, alx, aly);
   };
   stage_tile<T, PH_EULER, 2, K, TX, TY, NT, MODE, true>(a, k, tile_x, tile_y, begin, sm, fb, sx, sy,
                                                         flags, &e);
@@ -810,7 +905,7 @@ __global__ __launch_bounds__(NT, (EdgeOcc<T>::WAVES)) void k_stage_edges(StageAr
   if constexpr (K > 0) {
     // speeds of the new stage state feed the next stage's splitting; after
     // stage 3 they are the next step's stage-1 speeds (multi-step calls)
-    block_fold<NT>(sx, sy, flags, a.ctrl + (K < 3 ? 2 * K : 10), a.status,
+    block_fold<NT>(sx, sy, flags, a.fold + my_slot((int)gridDim.x) + 2 * K, a.status,
                    !a.replay && (K < 3 || a.fold_next));
   }
 }
@@ -872,7 +967,7 @@ __device__ __forceinline__ void batched_tile(const hweno_instance* __restrict__ 
   const auto begin = [&](double& dt, double& alx, double& aly) {
     alx = a.ctrl[2 * (K - 1)];
     aly = a.ctrl[2 * (K - 1) + 1];
-    return ran = stage_dt<2, K>(a.ctrl, a.dt_fixed, a.t_end, cfl, a.dx, a.dy, 0, leader, a.status, dt);
+    return ran = stage_dt<2, K>(a.ctrl, a.ctrl[6], a.ctrl[7], alx, aly, a.dt_fixed, a.t_end, cfl, a.dx, a.dy, 0, leader, a.status, dt);
   };
   const int lt = t - I.tile_begin[V];
   const int ntx = (I.nx + TX - 1) / TX;
@@ -1500,10 +1595,11 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
   }
 }
 
-// global speeds of a state: alpha[0..1] = max over cells (target pre-zeroed)
+// global speeds of a state: the maximum over cells into alpha[0..1], or into the
+// slots that begin there which a stage of stage_wgs workgroups reads; pre-zeroed
 template <typename T, int PHYS, int DIM>
 __global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, long long n,
-                                               Consts<T> k, double* alpha,
+                                               Consts<T> k, double* alpha, int stage_wgs,
                                                unsigned long long* status) {
   constexpr int M = Comps<PHYS, DIM>::M;
   T mx = T(0), my = T(0);
@@ -1518,7 +1614,7 @@ __global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, long lon
     mx = (dbits(double(sx)) > dbits(double(mx))) ? sx : mx;
     my = (dbits(double(sy)) > dbits(double(my))) ? sy : my;
   }
-  block_fold<256>(mx, my, flags, alpha, status, true);
+  block_fold<256>(mx, my, flags, alpha + my_slot(stage_wgs), status, true);
 }
 
 // k_alpha over the fluid cells of a 2D Euler grid with an obstacle (solid
@@ -1526,7 +1622,8 @@ __global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, long lon
 template <typename T>
 __global__ __launch_bounds__(256) void k_alpha_obstacle(const T* __restrict__ S, int nx, int ny,
                                                         int oi, int oj, Consts<T> k,
-                                                        double* alpha, unsigned long long* status) {
+                                                        double* alpha, int stage_wgs,
+                                                        unsigned long long* status) {
   const long long n = (long long)nx * ny;
   T mx = T(0), my = T(0);
   uint32_t flags = 0;
@@ -1541,13 +1638,12 @@ __global__ __launch_bounds__(256) void k_alpha_obstacle(const T* __restrict__ S,
     mx = (dbits(double(sx)) > dbits(double(mx))) ? sx : mx;
     my = (dbits(double(sy)) > dbits(double(my))) ? sy : my;
   }
-  block_fold<256>(mx, my, flags, alpha, status, true);
+  block_fold<256>(mx, my, flags, alpha + my_slot(stage_wgs), status, true);
 }
 
-// Start of a step: stage speeds and dt from the replay record, or speeds
-// cleared for the speed reduction; the next-step speed slots ctrl[10..11]
-// are cleared for this step's stage 3 (multi-step calls fold into them).
-__global__ void k_begin(double* ctrl, const double* replay) {
+// Start of a step: stage speeds and dt from the replay record, or speeds and speed
+// slots cleared for the reductions.
+__global__ void k_begin(double* ctrl, double* fold, const double* replay) {
   const int t = threadIdx.x;
   if (replay) {
     if (t < 7) ctrl[t] = replay[t];
@@ -1555,37 +1651,43 @@ __global__ void k_begin(double* ctrl, const double* replay) {
     ctrl[t] = 0.0;
   }
   if (t == 10 || t == 11) ctrl[t] = 0.0;
+  if (!replay)
+    for (int q = t; q < NSLOT * SLOT_LEN; q += 64) fold[q] = 0.0;
 }
 
 __global__ void k_zero(double* p, int n) {
   if ((int)threadIdx.x < n) p[threadIdx.x] = 0.0;
 }
 
-// End of a step: time and step count, tape record.  begin_next: also start
-// the next step of a multi-step call (what k_begin does with take_next), so
-// consecutive steps need one small launch between them instead of two.
-__global__ void k_finish(double* ctrl, double* tape, int begin_next) {
-  if (threadIdx.x == 0) {
-    if (ctrl[6] > 0.0) {
-      ctrl[7] += ctrl[6];
-      ctrl[9] += 1.0;
-    } else {
-      // skipped step: the state is unchanged, so the next step's stage-1
-      // speeds (taken from ctrl[10..11] in multi-step calls) are this step's
-      ctrl[10] = ctrl[0];
-      ctrl[11] = ctrl[1];
-    }
-    if (tape) {
-      for (int q = 0; q < 10; ++q) tape[q] = ctrl[q];
-    }
-  }
+// End of a step: time and step count, tape record.  begin_next: also start the
+// next step of a multi-step call (what k_begin does), with the stage-1 speeds that
+// this step's third stage folded, or, after a skipped step, whose state is
+// unchanged, with this step's own; so consecutive steps need one small launch
+// between them instead of two.
+// One wave: entry t of the control block is lane t's, all of it loaded at once.
+__global__ __launch_bounds__(64) void k_finish(double* ctrl, double* fold, double* tape,
+                                               int begin_next) {
+  const int t = threadIdx.x;
+  double v = t < 10 ? gld((const double*)ctrl + t) : 0.0;
+  double* f = fold + (t & (NSLOT - 1)) * SLOT_LEN;
+  double nx = 0.0, ny = 0.0;
+  if (begin_next && t < NSLOT) nx = gld((const double*)f + 6), ny = gld((const double*)f + 7);
+  const double dt = __shfl(v, 6), ax = __shfl(v, 0), ay = __shfl(v, 1);
+  const bool ran = dt > 0.0;
+  if (ran && t == 7) v += dt;
+  if (ran && t == 9) v += 1.0;
+  if (tape && t < 10) gst(tape + t, v);
+  if (ran && (t == 7 || t == 9)) gst(ctrl + t, v);
   if (begin_next) {
-    __syncthreads();
-    const int t = threadIdx.x;
-    const double nxt = t < 2 ? ctrl[10 + t] : 0.0;
-    __syncthreads();
-    if (t < 6) ctrl[t] = nxt;
-    if (t == 10 || t == 11) ctrl[t] = 0.0;
+    if (t < 6) gst(ctrl + t, 0.0);
+    if (t < NSLOT) {
+      if (ran) gst(f, nx), gst(f + 1, ny);
+#pragma unroll
+      for (int q = 2; q < 8; ++q) gst(f + q, 0.0);
+    }
+  } else if (!ran) {
+    if (t == 10) gst(ctrl + 10, ax);
+    if (t == 11) gst(ctrl + 11, ay);
   }
 }
 
@@ -1911,6 +2013,8 @@ using namespace hweno;
 // for the life of the process.  On the host this name is only a handle for
 // hipGetSymbolAddress: kernels receive the device address it returns.
 static __device__ __align__(256) unsigned char scratch[HWENO_STATIC_SCRATCH_BYTES];
+// its speed slots
+static __device__ __align__(256) double scratch_fold[NSLOT * SLOT_LEN];
 
 namespace {
 
@@ -2095,7 +2199,7 @@ long long cells_of(const hweno_problem* p) {
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 struct WsLayout {
-  size_t ctrl, s1, s2, base, total;
+  size_t ctrl, s1, s2, base, fold, total;
 };
 
 WsLayout ws_layout(const hweno_problem* p) {
@@ -2105,7 +2209,8 @@ WsLayout ws_layout(const hweno_problem* p) {
   L.s1 = align256(HWENO_CTRL_LEN * sizeof(double));
   L.s2 = L.s1 + align256(fb * n_fields(p));
   L.base = L.s2 + align256(fb * n_fields(p));
-  L.total = L.base + align256(fb * n_comp(p) * p->dim);
+  L.fold = L.base + align256(fb * n_comp(p) * p->dim);
+  L.total = L.fold + NSLOT * SLOT_LEN * sizeof(double);
   return L;
 }
 
@@ -2243,12 +2348,12 @@ struct RunAlpha {
       if (p->obstacle[1] > 0) {
         k_alpha_obstacle<T><<<alpha_blocks(n), 256, 0, s>>>(
             (const T*)state, p->nx, p->ny, p->obstacle[0], p->obstacle[1], make_consts<T>(p),
-            alpha, status);
+            alpha, 0, status);
         return launch_check("alpha");
       }
     }
     k_alpha<T, PHYS, DIM><<<alpha_blocks(n), 256, 0, s>>>((const T*)state, n,
-                                                          make_consts<T>(p), alpha, status);
+                                                          make_consts<T>(p), alpha, 0, status);
     return launch_check("alpha");
   }
 };
@@ -2300,19 +2405,20 @@ struct RunLimit {
   }
 };
 
-// where one step keeps its control block, its two stage states and the
-// limited base derivatives
+// where one step keeps its control block, its two stage states, the limited base
+// derivatives and the speed slots
 struct StepBufs {
   double* ctrl;
   void* s1;
   void* s2;
   void* base;
+  double* fold;
 };
 
 StepBufs ws_bufs(const hweno_problem* p, void* ws) {
   const WsLayout L = ws_layout(p);
   char* w = (char*)ws;
-  return StepBufs{(double*)(w + L.ctrl), w + L.s1, w + L.s2, w + L.base};
+  return StepBufs{(double*)(w + L.ctrl), w + L.s1, w + L.s2, w + L.base, (double*)(w + L.fold)};
 }
 
 struct RunStep {
@@ -2334,23 +2440,24 @@ struct RunStep {
     };
     const long long n = cells_of(p);
     const Consts<T> k = make_consts<T>(p);
-    if (!(take_next && !replay)) k_begin<<<1, 64, 0, s>>>(ctrl, replay);
+    if (!(take_next && !replay)) k_begin<<<1, 64, 0, s>>>(ctrl, b.fold, replay);
     if (!replay && !take_next) {
       bool done = false;
       if constexpr (PHYS == PH_EULER && DIM == 2) {
         if (p->obstacle[1] > 0) {
           k_alpha_obstacle<T><<<alpha_blocks(n), 256, 0, s>>>(
-              (const T*)state, p->nx, p->ny, p->obstacle[0], p->obstacle[1], k, ctrl,
+              (const T*)state, p->nx, p->ny, p->obstacle[0], p->obstacle[1], k, b.fold, (int)stage_grid(DIM, p->nx, p->ny).x,
               (unsigned long long*)(ctrl + 8));
           done = true;
         }
       }
       if (!done)
         k_alpha<T, PHYS, DIM><<<alpha_blocks(n), 256, 0, s>>>(
-            (const T*)state, n, k, ctrl, (unsigned long long*)(ctrl + 8));
+            (const T*)state, n, k, b.fold, (int)stage_grid(DIM, p->nx, p->ny).x, (unsigned long long*)(ctrl + 8));
     }
     StageArgs<T> a = base_args<T, PHYS, DIM>(p);
     a.ctrl = ctrl;
+    a.fold = b.fold;
     a.status = (unsigned long long*)(ctrl + 8);
     a.st0 = (const T*)state;
     a.base = (T*)b.base;
@@ -2391,7 +2498,7 @@ struct RunStep {
             timed(s, [&] { k_stage_edges<T, 3, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k, e); });
           };
           with_mode(p, edge_stages);
-          k_finish<<<1, 64, 0, s>>>(ctrl, tape, fold_next && !replay ? 1 : 0);
+          k_finish<<<1, 64, 0, s>>>(ctrl, b.fold, tape, fold_next && !replay ? 1 : 0);
           return launch_check("rk3_step");
         }
       }
@@ -2399,7 +2506,7 @@ struct RunStep {
     } else {
       stages(std::integral_constant<int, MODE_COMP>{});
     }
-    k_finish<<<1, 64, 0, s>>>(ctrl, tape, fold_next && !replay ? 1 : 0);
+    k_finish<<<1, 64, 0, s>>>(ctrl, b.fold, tape, fold_next && !replay ? 1 : 0);
     return launch_check("rk3_step");
   }
 };
@@ -2726,8 +2833,9 @@ hweno_status batch_common_ok(const hweno_problem* common) {
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
+void* g_scratch_fold[kMaxDevices] = {};
 
-hweno_status static_scratch(hipStream_t s, void** out) {
+hweno_status static_scratch(hipStream_t s, void** out, double** fold) {
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return fail(HWENO_ERR_LAUNCH, "hipGetDevice: %s", hipGetErrorString(e));
@@ -2747,9 +2855,16 @@ hweno_status static_scratch(hipStream_t s, void** out) {
     if (e != hipSuccess || !ptr)
       return fail(HWENO_ERR_LAUNCH, "hipGetSymbolAddress(scratch) on device %d: %s", dev,
                   hipGetErrorString(e));
+    void* slots = nullptr;
+    e = hipGetSymbolAddress(&slots, HIP_SYMBOL(scratch_fold));
+    if (e != hipSuccess || !slots)
+      return fail(HWENO_ERR_LAUNCH, "hipGetSymbolAddress(scratch_fold) on device %d: %s", dev,
+                  hipGetErrorString(e));
     g_scratch_ptr[dev] = ptr;
+    g_scratch_fold[dev] = slots;
   }
   *out = g_scratch_ptr[dev];
+  *fold = (double*)g_scratch_fold[dev];
   return HWENO_OK;
 }
 
@@ -2853,16 +2968,17 @@ hweno_status hweno_rk3_step_static(const hweno_problem* prob, void* state, doubl
   // the stage states and base derivatives, laid out as in a workspace but
   // without its control block
   const WsLayout L = ws_layout(prob);
-  const size_t need = L.total - L.s1;
+  const size_t need = L.fold - L.s1;
   if (need > (size_t)HWENO_STATIC_SCRATCH_BYTES)
     return fail(HWENO_ERR_WORKSPACE,
                 "grid too large for the static scratch: needs %zu bytes, the maximum is %zu",
                 need, (size_t)HWENO_STATIC_SCRATCH_BYTES);
   void* base = nullptr;
-  st = static_scratch((hipStream_t)stream, &base);
+  double* fold = nullptr;
+  st = static_scratch((hipStream_t)stream, &base, &fold);
   if (st) return st;
   char* w = (char*)base;
-  const StepBufs b{ctrl, w, w + (L.s2 - L.s1), w + (L.base - L.s1)};
+  const StepBufs b{ctrl, w, w + (L.s2 - L.s1), w + (L.base - L.s1), fold};
   st = dispatch<RunSteps>(prob, state, b, 1, dt_fixed, t_end, tape, replay, false,
                           (hipStream_t)stream);
   if (st) return st;
