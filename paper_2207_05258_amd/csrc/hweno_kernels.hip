@@ -1597,24 +1597,25 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
 
 // global speeds of a state: the maximum over cells into alpha[0..1], or into the
 // slots that begin there which a stage of stage_wgs workgroups reads; pre-zeroed
-template <typename T, int PHYS, int DIM>
-__global__ __launch_bounds__(256) void k_alpha(const T* __restrict__ S, long long n,
+// NT: 256 threads, or 1024 where every workgroup's atomics meet on one address.
+template <typename T, int PHYS, int DIM, int NT>
+__global__ __launch_bounds__(NT) void k_alpha(const T* __restrict__ S, long long n,
                                                Consts<T> k, double* alpha, int stage_wgs,
                                                unsigned long long* status) {
   constexpr int M = Comps<PHYS, DIM>::M;
   T mx = T(0), my = T(0);
   uint32_t flags = 0;
-  for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += 256ll * gridDim.x) {
+  for (long long i = (long long)blockIdx.x * NT + threadIdx.x; i < n; i += (long long)NT * gridDim.x) {
     T U[M];
 #pragma unroll
-    for (int c = 0; c < M; ++c) U[c] = S[c * n + i];
+    for (int c = 0; c < M; ++c) U[c] = gld(S + c * n + i);
     T sx, sy;
     point_speeds<T, PHYS, DIM>(U, k, sx, sy, flags);
     // bit-pattern max keeps NaN
     mx = (dbits(double(sx)) > dbits(double(mx))) ? sx : mx;
     my = (dbits(double(sy)) > dbits(double(my))) ? sy : my;
   }
-  block_fold<256>(mx, my, flags, alpha + my_slot(stage_wgs), status, true);
+  block_fold<NT>(mx, my, flags, alpha + my_slot(stage_wgs), status, true);
 }
 
 // k_alpha over the fluid cells of a 2D Euler grid with an obstacle (solid
@@ -2328,14 +2329,18 @@ dim3 stage_grid(int dim, int nx, int ny) {
   return dim3((nx + Tile<1>::TX - 1) / Tile<1>::TX);
 }
 
-// eight cells per thread: every workgroup ends in one atomic max on the same
-// two words, and at small grids a thousand workgroups finishing together
-// serialise there (512^2: 24 us with one cell per thread, 11 us with eight)
+// Workgroups of a speed reduction of 256 threads into the slots: two cells a thread
+// (eight single steps of 96 x 64: 317 us, with eight cells a thread 340 us).
 unsigned alpha_blocks(long long n) {
-  long long b = (n + 2047) / 2048;
-  if (b > 2048) b = 2048;
-  if (b < 1) b = 1;
-  return (unsigned)b;
+  return (unsigned)std::min<long long>(2048, std::max<long long>(1, (n + 511) / 512));
+}
+
+// Workgroups of 1024 threads of a reduction on one address, where each one's atomics
+// queue behind the others' (15 ns).  With the one stage that follows, 512 workgroups of
+// 256 threads, 256, 128 and 64 of 1024: 1024^2 FP32 76.9, 68.8, 67.4, 69.8 us; 2000^2
+// FP64 384.8, 355.5, 362.8, 384.3 us.
+unsigned alpha_blocks_one(long long n) {
+  return (unsigned)std::min<long long>(256, std::max<long long>(1, (n + 4095) / 4096));
 }
 
 struct RunAlpha {
@@ -2346,14 +2351,14 @@ struct RunAlpha {
     k_zero<<<1, 64, 0, s>>>(alpha, 2);
     if constexpr (PHYS == PH_EULER && DIM == 2) {
       if (p->obstacle[1] > 0) {
-        k_alpha_obstacle<T><<<alpha_blocks(n), 256, 0, s>>>(
+        k_alpha_obstacle<T><<<std::min(alpha_blocks(n), 256u), 256, 0, s>>>(
             (const T*)state, p->nx, p->ny, p->obstacle[0], p->obstacle[1], make_consts<T>(p),
             alpha, 0, status);
         return launch_check("alpha");
       }
     }
-    k_alpha<T, PHYS, DIM><<<alpha_blocks(n), 256, 0, s>>>((const T*)state, n,
-                                                          make_consts<T>(p), alpha, 0, status);
+    k_alpha<T, PHYS, DIM, 1024><<<alpha_blocks_one(n), 1024, 0, s>>>((const T*)state, n,
+                                                                     make_consts<T>(p), alpha, 0, status);
     return launch_check("alpha");
   }
 };
@@ -2452,7 +2457,7 @@ struct RunStep {
         }
       }
       if (!done)
-        k_alpha<T, PHYS, DIM><<<alpha_blocks(n), 256, 0, s>>>(
+        k_alpha<T, PHYS, DIM, 256><<<alpha_blocks(n), 256, 0, s>>>(
             (const T*)state, n, k, b.fold, (int)stage_grid(DIM, p->nx, p->ny).x, (unsigned long long*)(ctrl + 8));
     }
     StageArgs<T> a = base_args<T, PHYS, DIM>(p);

@@ -269,7 +269,7 @@ def rhs(S: torch.Tensor, prob: Problem, alpha_: Optional[torch.Tensor] = None,
     _require(S, prob, prob.nf, "state")
     L = out if out is not None else torch.empty_like(S)
     if alpha_ is None:
-        a = torch.zeros(2, dtype=torch.float64, device=S.device)
+        a = torch.empty(2, dtype=torch.float64, device=S.device)
         compute = 1
     else:
         a = _speeds(alpha_, S.device)
