@@ -301,7 +301,7 @@ hweno_status hweno_rk3_step_adjoint(const hweno_problem* prob, const void* state
                                     size_t ws_bytes, void* stream);
 
 /* ---------------------------------------------------------------------------
- * Batched 2D Euler: many independent grids advanced by one persistent launch
+ * Batched 2D Euler: many independent grids advanced by one launch
  * per Runge-Kutta stage (the same stage computation as hweno_rk3_step, per
  * instance: own speeds, own dt, own boundary conditions).
  *
@@ -338,27 +338,27 @@ hweno_status hweno_batch_prepare(const hweno_problem* common, hweno_instance* in
 hweno_status hweno_batch_tile_map(const hweno_instance* inst, int32_t n_inst, int32_t variant,
                                   int32_t* map, int32_t total_tiles);
 
-/* One SSP-RK3 step of every instance: wave speeds, three persistent stage
- * launches striding over the flattened tile list, and the per-instance time
+/* One SSP-RK3 step of every instance: wave speeds, three stage
+ * launches over the flattened tile list, and the per-instance time
  * update.  Enqueues six kernels and nothing else, so it can be captured in a
  * hipGraph.  inst_dev: device copy of the prepared descriptors; tile_map_dev:
  * device copy of the tile map of `variant`; total_tiles: the prepared count
- * for `variant`; blocks: persistent grid size (0 = up to 8 workgroups per
- * compute unit). */
+ * for `variant`; blocks: workgroups that walk the tile list, at most one per tile
+ * (0 = one per tile). */
 hweno_status hweno_rk3_step_batched(const hweno_problem* common, const hweno_instance* inst_dev,
                                     const int32_t* tile_map_dev, int32_t n_inst,
                                     int32_t total_tiles, int32_t variant, int32_t blocks,
                                     void* stream);
 
-/* Autotuner of the batched stepper: the tile variant and the persistent grid
+/* Autotuner of the batched stepper: the tile variant and the grid
  * size of hweno_rk3_step_batched for one batch, chosen by measurement.  For
  * every tile variant (0 = 16 x 15 cells, 1 = 32 x 7 cells) and every grid
- * candidate -- the stage kernel's resident capacity (blocks = 0), 2 and 4
+ * candidate -- the stage kernel's resident capacity, 2 and 4
  * workgroups per compute unit, and one workgroup per tile -- it runs one
  * warm-up step and then `trials` steps between two hipEvents on `stream`,
  * and returns the fastest pair in *variant, *blocks (pass them to
  * hweno_rk3_step_batched; *blocks is the workgroup count the fastest
- * candidate launched, the resident capacity resolved, never 0).  The steps are real steps of the instances that
+ * candidate launched, never 0).  The steps are real steps of the instances that
  * inst_dev describes, so give it descriptors of scratch copies (states and
  * workspaces) of the batch to tune; their control blocks follow the usual
  * rules.  tile_maps_dev: host array of HWENO_BATCH_VARIANTS device tile maps;
