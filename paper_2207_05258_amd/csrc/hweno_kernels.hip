@@ -471,7 +471,7 @@ __device__ __forceinline__ void obstacle_mirror(const StageArgs<T>& a, const Edg
 // ---------------------------------------------------------------------------
 // MODE: which fields the reconstruction and the limiter of the Euler equations
 // work on, separate instantiations because a branch between them costs the
-// default kernels their registers (FP64: 250 instead of 218 VGPRs).  The scalar
+// default kernels their registers (FP64: 250 instead of 220 VGPRs).  The scalar
 // laws use MODE_COMP.
 // EDG: edge-described sides (2D Euler; a separate instantiation), read from *e.
 enum {
@@ -829,11 +829,11 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
 // ---------------------------------------------------------------------------
 // Resident waves per SIMD the stage kernels are compiled for (the register
 // budget is 512 / WAVES per lane; LDS allows five FP32 and two FP64
-// workgroups per CU).  FP32: four, where every stage kernel fits (104-108
+// workgroups per CU).  FP32: four, where every stage kernel fits (123-128
 // VGPRs); at five (96) they spill 40 B per lane: 2.583 against 2.606 ms for
 // four steps of 2047 x 1531, and 5.09 against 5.65 ms for a step of 256
-// batched grids, whose persistent kernel spills most.  FP64: two (218 VGPRs,
-// no spills); a third would need 168 and spills 352 B.
+// batched grids walked by resident workgroups, whose kernel spills most.  FP64: two
+// (220-224 VGPRs, no spills); a third would need 168 and spills 352 B.
 template <typename T, int K>
 struct StageOcc {
   static constexpr int WAVES = sizeof(T) == 4 ? 4 : 2;
@@ -911,8 +911,8 @@ __global__ __launch_bounds__(NT, (EdgeOcc<T>::WAVES)) void k_stage_edges(StageAr
 }
 
 // ---------------------------------------------------------------------------
-// Batched 2D Euler: persistent kernels striding over the flattened tile list
-// of many independent instances.
+// Batched 2D Euler: kernels over the flattened tile list of many independent
+// instances, one tile per workgroup or striding.
 // ---------------------------------------------------------------------------
 template <int V>
 struct BatchTile;
