@@ -3049,7 +3049,8 @@ hweno_status hweno_rk3_step_adjoint(const hweno_problem* prob, const void* state
   if (empty(prob)) return ok();
   if (!state0 || !step_ws || !tape || !lam || !ws)
     return fail(HWENO_ERR_INVALID_ARG, "state0, step_ws, tape, lam and ws must be non-NULL");
-  if (step_ws_bytes < ws_layout(prob).total)
+  // the speed slots at its end are not read: a saved copy may lack them
+  if (step_ws_bytes < ws_layout(prob).fold)
     return fail(HWENO_ERR_WORKSPACE, "step workspace too small");
   if (ws_bytes < adj_layout(prob).total)
     return fail(HWENO_ERR_WORKSPACE, "adjoint workspace too small: %zu < %zu bytes", ws_bytes,
