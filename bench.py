@@ -281,7 +281,7 @@ def run_batched(steps: int, warmup: int, n_inst: int = 256, seed: int = 0):
     return {"value": b.cells * 3 * steps / wall, "unit": "cell-stage updates/s", "dtype": "f32",
             "instances": n_inst, "cells": b.cells, "variant": best[0], "blocks": best[1],
             "steps": steps, "ms_per_step": wall * 1e3 / steps, "failed_instances": bad,
-            "graph": "one hipGraph per step (speeds, 3 persistent stages, time update)"}
+            "graph": "one hipGraph per step (speeds, 3 stages, time update)"}
 
 
 def run_small(n: int = 4000, steps: int = 200):

@@ -513,7 +513,7 @@ AUTOTUNE_CANDIDATES = 4
 
 
 def autotune_batched(stepper: BatchedStepper, trials: int = 2):
-    """Tile variant and persistent grid size of ``stepper`` chosen by hweno_autotune.
+    """Tile variant and grid size of ``stepper`` chosen by hweno_autotune.
 
     The library times every (variant, grid) candidate on clones of the states
     (the originals are untouched) with hipEvents and returns the fastest; this
