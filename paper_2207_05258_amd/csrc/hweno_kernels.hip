@@ -338,7 +338,8 @@ __device__ __forceinline__ double step_dt(double alx, double aly, double dt_fixe
   } else {
     dt = cfl / (alx / dx + aly / dy);
   }
-  if (t_end > 0.0) dt = fmin(dt, t_end - t);
+  const double left = t_end - t;
+  if (t_end > 0.0 && dt > left) dt = left;  // a comparison: fmin would drop a NaN
   return (!(dt > 0.0) || !isfinite(dt)) ? 0.0 : dt;
 }
 
