@@ -643,17 +643,19 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
   }
   __syncthreads();
   // the interfaces' fluxes are twice f-hat, 8 h h-hat and 12 times the mixed flux
-  // of a derivative times its own cell size
+  // of a derivative times its own cell size.  LV and LW leave out one factor idx
+  // and idy until their own cell: the square of a cell size's reciprocal may leave
+  // the range of T where the results do not.
   if (owner) {
 #pragma unroll
     for (int c = 0; c < M; ++c) {
       const int b0 = (c * FR + ty) * FW + tx;
       LU[c] = (fb[b0] - fb[b0 + 1]) * (T(0.5) * idx);
       const int b1 = ((M + c) * FR + ty) * FW + tx;
-      LV[c] = (fb[b1] - fb[b1 + 1]) * (T(0.125) * idx * idx);
+      LV[c] = (fb[b1] - fb[b1 + 1]) * (T(0.125) * idx);
       if constexpr (DIM == 2) {
         const int b2 = ((2 * M + c) * FR + ty) * FW + tx;
-        LW[c] = (fb[b2] - fb[b2 + 1]) * (T(1.0 / 12.0) * idx * idy);
+        LW[c] = (fb[b2] - fb[b2 + 1]) * (T(1.0 / 12.0) * idx);
       }
     }
   }
@@ -698,9 +700,9 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
         const int b0 = (c * FR + ty) * FW + tx;
         LU[c] = mad(fb[b0] - fb[b0 + FW], T(0.5) * idy, LU[c]);
         const int b1 = ((M + c) * FR + ty) * FW + tx;
-        LW[c] = mad(fb[b1] - fb[b1 + FW], T(0.125) * idy * idy, LW[c]);
+        LW[c] = mad(fb[b1] - fb[b1 + FW], T(0.125) * idy, LW[c]);
         const int b2 = ((2 * M + c) * FR + ty) * FW + tx;
-        LV[c] = mad(fb[b2] - fb[b2 + FW], T(1.0 / 12.0) * idx * idy, LV[c]);
+        LV[c] = mad(fb[b2] - fb[b2 + FW], T(1.0 / 12.0) * idy, LV[c]);
       }
     }
   }
@@ -724,8 +726,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
 #pragma unroll
     for (int c = 0; c < M; ++c) {
       gst(a.out + c * fs + g, LU[c]);
-      gst(a.out + (M + c) * fs + g, LV[c]);
-      if constexpr (DIM == 2) gst(a.out + (2 * M + c) * fs + g, LW[c]);
+      gst(a.out + (M + c) * fs + g, LV[c] * idx);
+      if constexpr (DIM == 2) gst(a.out + (2 * M + c) * fs + g, LW[c] * idy);
     }
   } else {
     // S^_k = (U_k, limited derivatives of S_k)
@@ -795,8 +797,8 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
 #pragma unroll
     for (int c = 0; c < M; ++c) {
       L[c] = LU[c];
-      L[M + c] = LV[c];
-      if constexpr (DIM == 2) L[2 * M + c] = LW[c];
+      L[M + c] = LV[c] * idx;
+      if constexpr (DIM == 2) L[2 * M + c] = LW[c] * idy;
     }
     const T tdt = T(dt);
     T out[NF];
@@ -1817,7 +1819,7 @@ __global__ __launch_bounds__(NT) void k_steps_1d(StageArgs<T> a, Consts<T> k, T*
 #pragma unroll
           for (int c = 0; c < M; ++c) {
             L[c] = (fb[c * NT + tid] - fb[c * NT + tid + 1]) * (T(0.5) * idx);
-            L[M + c] = (fb[(M + c) * NT + tid] - fb[(M + c) * NT + tid + 1]) * (T(0.125) * idx * idx);
+            L[M + c] = (fb[(M + c) * NT + tid] - fb[(M + c) * NT + tid + 1]) * (T(0.125) * idx) * idx;
             Sh[c] = cur[c];
             Sh[M + c] = cur[M + c];
           }

@@ -1,6 +1,8 @@
 """What hweno.h promises of a step on every path that takes it: grids that one workgroup
 holds (1D), grids by launches of each way of reading the speeds (1D, 2D, edge-described
 sides), the static step and batched grids."""
+import dataclasses
+
 import pytest
 import torch
 
@@ -70,3 +72,44 @@ def test_nan_speed_skips_a_batched_step_clipped_to_t_end(blocks):
     _assert_skipped(b.ctrl(1), states[1], before[1], 0.0, blocks)
     for q in (0, 2):    # the others are stepped
         assert float(b.ctrl(q)[6]) > 0.0 and not torch.equal(states[q], before[q])
+
+
+# ---- cell sizes whose square leaves the range of the type ----
+# Lengths of 2^69 and 2^-67 around one, with fields of 2^16 and 2^-16 (in FP32 the square
+# of an indicator leaves the range near 2^20): 1 / dx^2 is 2^-138
+# and 2^134 in FP32 (11 bits of it and none), while the fields and the operator stay
+# normal.  Against the same call in FP64, in the norms of one step in FP32 (1e-5 of the
+# size of U; derivatives times their cell size; rates in units of speed over cell size).
+SCALES = [(69, 16), (-67, -16)]
+
+
+def _scaled_grid(dim, k, j):
+    w = hi.euler1d_piecewise(64, 3) if dim == 1 else hi.roughened(hi.euler2d_random_smooth(40, 33, 5), 7)
+    m, S = dim + 2, torch.as_tensor(w.S).clone()
+    if dim == 1:
+        S[m:] += 0.05 / w.dx * (2 * torch.rand(S[m:].shape, generator=torch.Generator().manual_seed(7), dtype=S.dtype) - 1)
+    for d, (old, new) in enumerate(((w.dx, 1.3), (w.dy, 1.4))[:dim]):
+        S[m * (1 + d):m * (2 + d)] *= old / new * 2.0 ** -k
+    S = (S * 2.0 ** j).float().cuda().contiguous()
+    n = dict(dim=1, nx=64) if dim == 1 else dict(dim=2, nx=40, ny=33)
+    return S, h.Problem(physics="euler", dtype=torch.float32, dx=1.3 * 2.0 ** k, dy=1.4 * 2.0 ** k,
+                        eps=1e-6 * 2.0 ** (2 * j), bc_x=w.bc_x, bc_y=w.bc_y, **n)
+
+
+@pytest.mark.parametrize("k,j", SCALES)
+@pytest.mark.parametrize("dim", [1, 2])
+def test_operator_and_step_at_extreme_cell_sizes(dim, k, j):
+    S, prob = _scaled_grid(dim, k, j)
+    X, q = S.double(), dataclasses.replace(prob, dtype=torch.float64)
+    m, size = prob.m, float(X[:prob.m].abs().max())
+    unit = [1.0] * m + [prob.dx] * m + [prob.dy] * m    # of U over each field
+    speed = float(h.alpha(X, q).max())
+    rate = h.rhs(S, prob).double(), h.rhs(X, q)
+    A, B = S.clone(), X.clone()
+    h.Stepper(prob).step(A)
+    h.Stepper(q).step(B)
+    for f in range(prob.nf):
+        for name, (a, b), s in (("rhs", rate, min(prob.dx, prob.dy) / speed), ("step", (A.double(), B), 1.0)):
+            assert torch.isfinite(a[f]).all(), (name, f)
+            err = float((a[f] - b[f]).abs().max()) * unit[f] * s
+            assert err <= 1e-5 * size, (name, f, err / size)
