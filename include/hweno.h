@@ -173,9 +173,11 @@ typedef struct {
  * law) with hweno_last_error() set. */
 hweno_status hweno_validate(const hweno_problem* prob);
 
-/* Bytes of device workspace hweno_rk3_step needs for `prob`
+/* Bytes of device workspace for hweno_rk3_step on `prob`
  * (control block, two stage states, the limited base derivatives and 1 KiB of
- * partial speeds).
+ * partial speeds).  A workspace without that last 1 KiB is accepted as well, with
+ * the same results: its speeds are then folded into one place, which costs
+ * grids of some hundred workgroups up to a third of their step.
  * Returns 0 for an invalid problem. */
 size_t hweno_workspace_bytes(const hweno_problem* prob);
 
@@ -209,8 +211,8 @@ hweno_status hweno_limit(const hweno_problem* prob, const void* state,
  *   derivatives) used in the update only and L always evaluated on the
  *   unlimited state.  Each stage recomputes the wave speeds of its own input.
  * state: device, in/out.
- * ws: device workspace of at least hweno_workspace_bytes(prob) bytes, 256-byte
- *   aligned; its first HWENO_CTRL_LEN doubles are the step control block.
+ * ws: device workspace of at least hweno_workspace_bytes(prob) bytes (or 1 KiB
+ *   less, see there), 256-byte aligned; its first HWENO_CTRL_LEN doubles are the step control block.
  *   Zero the control block before the first step of a run (t and the status
  *   word accumulate there across calls).
  * dt_fixed: > 0 uses this time step; otherwise dt = cfl dx / alpha_x (1D) or

@@ -44,6 +44,7 @@ struct StageArgs {
   T* base;            // limited derivatives of S^n (written by stage 1, read by 2, 3)
   double* ctrl;       // step control block (stages only)
   double* fold;       // speed slots (stages only; see NSLOT)
+  int slots;          // how many of them this grid uses: 1 or NSLOT
   unsigned long long* status;  // status word, or NULL
   const double* alpha;  // speeds for K == 0
   int nx, ny, bc_x, bc_y;
@@ -196,11 +197,12 @@ __device__ __forceinline__ T wave_max(T x) {
 // for q = 3 those of the next step's first stage.
 // SLOT_FEW workgroups or fewer do not queue long enough to pay for reading several
 // lines (eight steps of 60 x 60, 16 workgroups: 288 us on one slot, 296 on eight; 160
-// x 120, 80 workgroups: 337 and 298): they use slot 0 alone.
+// x 120, 80 workgroups: 337 and 298): they use slot 0 alone, as any grid does whose
+// workspace has no room for more (ws_bufs).
 constexpr int NSLOT = 8, SLOT_LEN = 16, SLOT_FEW = 48;
 
-__device__ __forceinline__ int my_slot(int workgroups) {
-  return workgroups > SLOT_FEW ? (int)(blockIdx.x & (NSLOT - 1)) * SLOT_LEN : 0;
+__device__ __forceinline__ int my_slot(int slots) {
+  return slots > 1 ? (int)(blockIdx.x & (NSLOT - 1)) * SLOT_LEN : 0;
 }
 
 // The maxima over the slots, in two ways; NaN wins.  By lanes (0..7 the x-speeds, 8..15
@@ -383,10 +385,9 @@ template <typename T, int K>
 __device__ __forceinline__ Early read_early(const StageArgs<T>& a) {
   Early r = {0.0, 0.0, 0.0, 0.0, 0.0};
   if constexpr (K > 0) {
-    const int n = (int)gridDim.x;
     r.dt = a.ctrl[6], r.time = a.ctrl[7];
     r.f0 = a.fold[2 * (K - 1)], r.f1 = a.fold[2 * (K - 1) + 1];
-    if (n > SLOT_FEW && n <= slot_lanes<T>()) r.lanes = slot_load(a.fold, K - 1);
+    if (a.slots > 1 && (int)gridDim.x <= slot_lanes<T>()) r.lanes = slot_load(a.fold, K - 1);
   }
   return r;
 }
@@ -406,10 +407,9 @@ __device__ __forceinline__ bool grid_begin(const StageArgs<T>& a, const Early& e
       alx = a.ctrl[2 * (K - 1)];
       aly = a.ctrl[2 * (K - 1) + 1];
     } else {
-      const int n = (int)gridDim.x;
-      if (n <= SLOT_FEW)
+      if (a.slots == 1)
         alx = early.f0, aly = early.f1;
-      else if (n <= slot_lanes<T>())
+      else if ((int)gridDim.x <= slot_lanes<T>())
         slot_max(early.lanes, alx, aly);
       else
         slot_max_scalar(a.fold, K - 1, alx, aly);
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(NT, (StageOcc<T, K>::WAVES)) void k_stage(StageArgs
   if constexpr (K > 0) {
     // speeds of the new stage state feed the next stage's splitting; after
     // stage 3 they are the next step's stage-1 speeds (multi-step calls)
-    block_fold<NT>(sx, sy, flags, a.fold + my_slot((int)gridDim.x) + 2 * K, a.status,
+    block_fold<NT>(sx, sy, flags, a.fold + my_slot(a.slots) + 2 * K, a.status,
                    !a.replay && (K < 3 || a.fold_next));
   }
 }
@@ -908,7 +908,7 @@ __global__ __launch_bounds__(NT, (EdgeOcc<T>::WAVES)) void k_stage_edges(StageAr
   if constexpr (K > 0) {
     // speeds of the new stage state feed the next stage's splitting; after
     // stage 3 they are the next step's stage-1 speeds (multi-step calls)
-    block_fold<NT>(sx, sy, flags, a.fold + my_slot((int)gridDim.x) + 2 * K, a.status,
+    block_fold<NT>(sx, sy, flags, a.fold + my_slot(a.slots) + 2 * K, a.status,
                    !a.replay && (K < 3 || a.fold_next));
   }
 }
@@ -1598,12 +1598,12 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
   }
 }
 
-// global speeds of a state: the maximum over cells into alpha[0..1], or into the
-// slots that begin there which a stage of stage_wgs workgroups reads; pre-zeroed
+// global speeds of a state: the maximum over cells into the first two entries of
+// `slots` slots that begin at alpha; pre-zeroed
 // NT: 256 threads, or 1024 where every workgroup's atomics meet on one address.
 template <typename T, int PHYS, int DIM, int NT>
 __global__ __launch_bounds__(NT) void k_alpha(const T* __restrict__ S, long long n,
-                                               Consts<T> k, double* alpha, int stage_wgs,
+                                               Consts<T> k, double* alpha, int slots,
                                                unsigned long long* status) {
   constexpr int M = Comps<PHYS, DIM>::M;
   T mx = T(0), my = T(0);
@@ -1618,7 +1618,7 @@ __global__ __launch_bounds__(NT) void k_alpha(const T* __restrict__ S, long long
     mx = (dbits(double(sx)) > dbits(double(mx))) ? sx : mx;
     my = (dbits(double(sy)) > dbits(double(my))) ? sy : my;
   }
-  block_fold<NT>(mx, my, flags, alpha + my_slot(stage_wgs), status, true);
+  block_fold<NT>(mx, my, flags, alpha + my_slot(slots), status, true);
 }
 
 // k_alpha over the fluid cells of a 2D Euler grid with an obstacle (solid
@@ -1626,7 +1626,7 @@ __global__ __launch_bounds__(NT) void k_alpha(const T* __restrict__ S, long long
 template <typename T>
 __global__ __launch_bounds__(256) void k_alpha_obstacle(const T* __restrict__ S, int nx, int ny,
                                                         int oi, int oj, Consts<T> k,
-                                                        double* alpha, int stage_wgs,
+                                                        double* alpha, int slots,
                                                         unsigned long long* status) {
   const long long n = (long long)nx * ny;
   T mx = T(0), my = T(0);
@@ -1642,12 +1642,12 @@ __global__ __launch_bounds__(256) void k_alpha_obstacle(const T* __restrict__ S,
     mx = (dbits(double(sx)) > dbits(double(mx))) ? sx : mx;
     my = (dbits(double(sy)) > dbits(double(my))) ? sy : my;
   }
-  block_fold<256>(mx, my, flags, alpha + my_slot(stage_wgs), status, true);
+  block_fold<256>(mx, my, flags, alpha + my_slot(slots), status, true);
 }
 
 // Start of a step: stage speeds and dt from the replay record, or speeds and speed
 // slots cleared for the reductions.
-__global__ void k_begin(double* ctrl, double* fold, const double* replay) {
+__global__ void k_begin(double* ctrl, double* fold, int slots, const double* replay) {
   const int t = threadIdx.x;
   if (replay) {
     if (t < 7) ctrl[t] = replay[t];
@@ -1656,7 +1656,7 @@ __global__ void k_begin(double* ctrl, double* fold, const double* replay) {
   }
   if (t == 10 || t == 11) ctrl[t] = 0.0;
   if (!replay)
-    for (int q = t; q < NSLOT * SLOT_LEN; q += 64) fold[q] = 0.0;
+    for (int q = t; q < slots * SLOT_LEN; q += 64) fold[q] = 0.0;
 }
 
 __global__ void k_zero(double* p, int n) {
@@ -1669,13 +1669,13 @@ __global__ void k_zero(double* p, int n) {
 // unchanged, with this step's own; so consecutive steps need one small launch
 // between them instead of two.
 // One wave: entry t of the control block is lane t's, all of it loaded at once.
-__global__ __launch_bounds__(64) void k_finish(double* ctrl, double* fold, double* tape,
+__global__ __launch_bounds__(64) void k_finish(double* ctrl, double* fold, int slots, double* tape,
                                                int begin_next) {
   const int t = threadIdx.x;
   double v = t < 10 ? gld((const double*)ctrl + t) : 0.0;
   double* f = fold + (t & (NSLOT - 1)) * SLOT_LEN;
   double nx = 0.0, ny = 0.0;
-  if (begin_next && t < NSLOT) nx = gld((const double*)f + 6), ny = gld((const double*)f + 7);
+  if (begin_next && t < slots) nx = gld((const double*)f + 6), ny = gld((const double*)f + 7);
   const double dt = __shfl(v, 6), ax = __shfl(v, 0), ay = __shfl(v, 1);
   const bool ran = dt > 0.0;
   if (ran && t == 7) v += dt;
@@ -1684,7 +1684,7 @@ __global__ __launch_bounds__(64) void k_finish(double* ctrl, double* fold, doubl
   if (ran && (t == 7 || t == 9)) gst(ctrl + t, v);
   if (begin_next) {
     if (t < 6) gst(ctrl + t, 0.0);
-    if (t < NSLOT) {
+    if (t < slots) {
       if (ran) gst(f, nx), gst(f + 1, ny);
 #pragma unroll
       for (int q = 2; q < 8; ++q) gst(f + q, 0.0);
@@ -2367,12 +2367,12 @@ struct RunAlpha {
       if (p->obstacle[1] > 0) {
         k_alpha_obstacle<T><<<std::min(alpha_blocks(n), 256u), 256, 0, s>>>(
             (const T*)state, p->nx, p->ny, p->obstacle[0], p->obstacle[1], make_consts<T>(p),
-            alpha, 0, status);
+            alpha, 1, status);
         return launch_check("alpha");
       }
     }
     k_alpha<T, PHYS, DIM, 1024><<<alpha_blocks_one(n), 1024, 0, s>>>((const T*)state, n,
-                                                                     make_consts<T>(p), alpha, 0, status);
+                                                                     make_consts<T>(p), alpha, 1, status);
     return launch_check("alpha");
   }
 };
@@ -2441,19 +2441,26 @@ struct RunLimit {
 };
 
 // where one step keeps its control block, its two stage states, the limited base
-// derivatives and the speed slots
+// derivatives and the speed slots, and how many of these there are
 struct StepBufs {
   double* ctrl;
   void* s1;
   void* s2;
   void* base;
   double* fold;
+  int slots;
 };
 
-StepBufs ws_bufs(const hweno_problem* p, void* ws) {
+// A workspace that ends before the slots (L.fold bytes or more) has one of them behind
+// the control block, in the rest of its 256 bytes.
+static_assert((HWENO_CTRL_LEN + SLOT_LEN) * sizeof(double) <= 256, "one slot fits behind the control block");
+StepBufs ws_bufs(const hweno_problem* p, void* ws, size_t ws_bytes) {
   const WsLayout L = ws_layout(p);
   char* w = (char*)ws;
-  return StepBufs{(double*)(w + L.ctrl), w + L.s1, w + L.s2, w + L.base, (double*)(w + L.fold)};
+  double* ctrl = (double*)(w + L.ctrl);
+  const bool all = ws_bytes >= L.total;
+  return StepBufs{ctrl, w + L.s1, w + L.s2, w + L.base,
+                  all ? (double*)(w + L.fold) : ctrl + HWENO_CTRL_LEN, all ? NSLOT : 1};
 }
 
 struct RunStep {
@@ -2475,24 +2482,27 @@ struct RunStep {
     };
     const long long n = cells_of(p);
     const Consts<T> k = make_consts<T>(p);
-    if (!(take_next && !replay)) k_begin<<<1, 64, 0, s>>>(ctrl, b.fold, replay);
+    const dim3 grid = stage_grid(DIM, p->nx, p->ny);
+    const int slots = (int)grid.x > SLOT_FEW ? b.slots : 1;
+    if (!(take_next && !replay)) k_begin<<<1, 64, 0, s>>>(ctrl, b.fold, slots, replay);
     if (!replay && !take_next) {
       bool done = false;
       if constexpr (PHYS == PH_EULER && DIM == 2) {
         if (p->obstacle[1] > 0) {
           k_alpha_obstacle<T><<<alpha_blocks(n), 256, 0, s>>>(
-              (const T*)state, p->nx, p->ny, p->obstacle[0], p->obstacle[1], k, b.fold, (int)stage_grid(DIM, p->nx, p->ny).x,
+              (const T*)state, p->nx, p->ny, p->obstacle[0], p->obstacle[1], k, b.fold, slots,
               (unsigned long long*)(ctrl + 8));
           done = true;
         }
       }
       if (!done)
         k_alpha<T, PHYS, DIM, 256><<<alpha_blocks(n), 256, 0, s>>>(
-            (const T*)state, n, k, b.fold, (int)stage_grid(DIM, p->nx, p->ny).x, (unsigned long long*)(ctrl + 8));
+            (const T*)state, n, k, b.fold, slots, (unsigned long long*)(ctrl + 8));
     }
     StageArgs<T> a = base_args<T, PHYS, DIM>(p);
     a.ctrl = ctrl;
     a.fold = b.fold;
+    a.slots = slots;
     a.status = (unsigned long long*)(ctrl + 8);
     a.st0 = (const T*)state;
     a.base = (T*)b.base;
@@ -2503,7 +2513,6 @@ struct RunStep {
     T* s1 = (T*)b.s1;
     T* s2 = (T*)b.s2;
     constexpr int TX = Tile<DIM>::TX, TY = Tile<DIM>::TY, NT = Tile<DIM>::NT;
-    const dim3 grid = stage_grid(DIM, a.nx, a.ny);
     auto stages = [&](auto mode) {
       constexpr int MODE = decltype(mode)::value;
       a.in = (const T*)state;
@@ -2533,7 +2542,7 @@ struct RunStep {
             timed(s, [&] { k_stage_edges<T, 3, TX, TY, NT, MODE><<<grid, NT, 0, s>>>(a, k, e); });
           };
           with_mode(p, edge_stages);
-          k_finish<<<1, 64, 0, s>>>(ctrl, b.fold, tape, fold_next && !replay ? 1 : 0);
+          k_finish<<<1, 64, 0, s>>>(ctrl, b.fold, slots, tape, fold_next && !replay ? 1 : 0);
           return launch_check("rk3_step");
         }
       }
@@ -2541,7 +2550,7 @@ struct RunStep {
     } else {
       stages(std::integral_constant<int, MODE_COMP>{});
     }
-    k_finish<<<1, 64, 0, s>>>(ctrl, b.fold, tape, fold_next && !replay ? 1 : 0);
+    k_finish<<<1, 64, 0, s>>>(ctrl, b.fold, slots, tape, fold_next && !replay ? 1 : 0);
     return launch_check("rk3_step");
   }
 };
@@ -2958,13 +2967,13 @@ hweno_status hweno_rk3_step(const hweno_problem* prob, void* state, void* ws, si
   if (st) return st;
   if (empty(prob)) return ok();
   if (!state || !ws) return fail(HWENO_ERR_INVALID_ARG, "state and ws must be non-NULL");
-  const size_t need = ws_layout(prob).total;
+  const size_t need = ws_layout(prob).fold;  // the slots are not required (ws_bufs)
   if (ws_bytes < need)
     return fail(HWENO_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, need);
   if (((uintptr_t)ws & 255u) != 0) return fail(HWENO_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   if (!std::isfinite(dt_fixed) || !std::isfinite(t_end))
     return fail(HWENO_ERR_INVALID_ARG, "dt_fixed and t_end must be finite");
-  st = dispatch<RunSteps>(prob, state, ws_bufs(prob, ws), 1, dt_fixed, t_end, tape, replay, true,
+  st = dispatch<RunSteps>(prob, state, ws_bufs(prob, ws, ws_bytes), 1, dt_fixed, t_end, tape, replay, true,
                           (hipStream_t)stream);
   if (st) return st;
   return ok();
@@ -2978,13 +2987,13 @@ hweno_status hweno_rk3_steps(const hweno_problem* prob, void* state, void* ws, s
   if (n_steps < 0) return fail(HWENO_ERR_INVALID_ARG, "n_steps must be >= 0");
   if (empty(prob) || n_steps == 0) return ok();
   if (!state || !ws) return fail(HWENO_ERR_INVALID_ARG, "state and ws must be non-NULL");
-  const size_t need = ws_layout(prob).total;
+  const size_t need = ws_layout(prob).fold;  // the slots are not required (ws_bufs)
   if (ws_bytes < need)
     return fail(HWENO_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, need);
   if (((uintptr_t)ws & 255u) != 0) return fail(HWENO_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   if (!std::isfinite(dt_fixed) || !std::isfinite(t_end))
     return fail(HWENO_ERR_INVALID_ARG, "dt_fixed and t_end must be finite");
-  st = dispatch<RunSteps>(prob, state, ws_bufs(prob, ws), (int)n_steps, dt_fixed, t_end, tapes,
+  st = dispatch<RunSteps>(prob, state, ws_bufs(prob, ws, ws_bytes), (int)n_steps, dt_fixed, t_end, tapes,
                           (const double*)nullptr, true, (hipStream_t)stream);
   if (st) return st;
   return ok();
@@ -3013,7 +3022,7 @@ hweno_status hweno_rk3_step_static(const hweno_problem* prob, void* state, doubl
   st = static_scratch((hipStream_t)stream, &base, &fold);
   if (st) return st;
   char* w = (char*)base;
-  const StepBufs b{ctrl, w, w + (L.s2 - L.s1), w + (L.base - L.s1), fold};
+  const StepBufs b{ctrl, w, w + (L.s2 - L.s1), w + (L.base - L.s1), fold, NSLOT};
   st = dispatch<RunSteps>(prob, state, b, 1, dt_fixed, t_end, tape, replay, false,
                           (hipStream_t)stream);
   if (st) return st;
@@ -3101,7 +3110,7 @@ hweno_status hweno_batch_prepare(const hweno_problem* common, hweno_instance* in
     if (!std::isfinite(I.dt_fixed) || !std::isfinite(I.t_end))
       return fail(HWENO_ERR_INVALID_ARG, "instance %d: dt_fixed, t_end must be finite", q);
     const WsLayout L = ws_layout(&p);
-    I.ws_bytes = (int64_t)L.total;
+    I.ws_bytes = (int64_t)L.fold;  // a batch folds its speeds into the control blocks
     I.off_s1 = (int64_t)L.s1;
     I.off_s2 = (int64_t)L.s2;
     I.off_base = (int64_t)L.base;

@@ -113,3 +113,38 @@ def test_operator_and_step_at_extreme_cell_sizes(dim, k, j):
             assert torch.isfinite(a[f]).all(), (name, f)
             err = float((a[f] - b[f]).abs().max()) * unit[f] * s
             assert err <= 1e-5 * size, (name, f, err / size)
+
+
+# ---- a workspace that ends before the 1 KiB of partial speeds is taken, exactly to its end ----
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32], ids=["f64", "f32"])
+@pytest.mark.parametrize("kind", GRIDS)
+def test_workspace_without_partial_speeds(kind, dtype):
+    S, prob = _grid(kind, dtype)
+    need = h.workspace_bytes(prob) - 1024
+    out = []
+    for short in (False, True):
+        X, tapes = S.clone(), torch.zeros(4, h.hweno.CTRL_LEN, dtype=torch.float64, device="cuda")
+        raw = torch.full((need + 1024 + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        ws = raw[(-raw.data_ptr()) % 256:]
+        ws[:h.hweno.CTRL_LEN * 8] = 0
+        st = h.Stepper._over(prob, prob.c(), ws, need if short else need + 1024)
+        st.step(X, tape=tapes[0])
+        st.steps(X, 2, tapes=tapes[1:3])
+        st.step(X, dt=1e-5, tape=tapes[3])
+        if short:
+            assert bool((ws[need:] == 0xA5).all())     # nothing was written past its end
+        out.append((X, tapes[:, :10], st.ctrl[:12].clone(), ws[256:need].clone()))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    with pytest.raises(h.HwenoError, match="workspace too small"):
+        h.Stepper._over(prob, prob.c(), ws, need - 1).step(S.clone())
+
+
+def test_batched_workspaces_hold_no_partial_speeds():
+    ws = hi.batched_instances(2, 3, sizes=[(37, 29), (64, 7)])
+    states = [torch.as_tensor(w.S).cuda().contiguous() for w in ws]
+    b = h.BatchedStepper(states, [dict(dx=w.dx, dy=w.dy) for w in ws],
+                         h.Problem(dim=2, nx=1, ny=1, physics="euler", dtype=torch.float64))
+    for q, w in enumerate(ws):
+        prob = h.Problem(dim=2, nx=w.nx, ny=w.ny, physics="euler", dtype=torch.float64, dx=w.dx, dy=w.dy)
+        assert int(b._host[q].ws_bytes) == h.workspace_bytes(prob) - 1024
