@@ -386,7 +386,10 @@ hweno_status hweno_autotune(const hweno_problem* common, const hweno_instance* i
  * up the elapsed times and returns the number of timed launches and their
  * total duration in milliseconds (either pointer may be NULL), then stops
  * timing and releases the events.  hweno_timing_begin(0) stops without
- * reporting.  Timing adds two event records per stage launch. */
+ * reporting.  Timing adds two event records per stage launch and changes nothing
+ * else: it times the kernels that run without it.  1D grids of fewer than 512 cells
+ * (Euler) or 1024 (scalar laws) take up to 256 whole steps in one launch, which
+ * is one pair and counts as one. */
 hweno_status hweno_timing_begin(int32_t enable);
 hweno_status hweno_timing_end(int64_t* launches, double* total_ms);
 

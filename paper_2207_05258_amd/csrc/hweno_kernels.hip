@@ -2573,8 +2573,7 @@ struct RunSteps {
                           double t_end, double* tapes, const double* replay, bool may_time,
                           hipStream_t s) {
     if constexpr (DIM == 1) {
-      // the diagnostic timer counts stage launches: it sees the general path
-      if (p->nx < OneBlock<PHYS>::NT2 && !(may_time && g_timing.on)) {
+      if (p->nx < OneBlock<PHYS>::NT2) {
         StageArgs<T> a = base_args<T, PHYS, 1>(p);
         a.ctrl = b.ctrl;
         a.in = (const T*)state;
@@ -2590,10 +2589,16 @@ struct RunSteps {
           auto launch = [&](auto mode) {
             constexpr int MODE = decltype(mode)::value;
             constexpr int NT1 = OneBlock<PHYS>::NT1, NT2 = OneBlock<PHYS>::NT2;
-            if (p->nx < NT1)
-              k_steps_1d<T, PHYS, NT1, MODE><<<1, NT1, 0, s>>>(a, k, (T*)b.s1, (T*)b.s2, tp, replay, m);
+            auto steps = [&] {
+              if (p->nx < NT1)
+                k_steps_1d<T, PHYS, NT1, MODE><<<1, NT1, 0, s>>>(a, k, (T*)b.s1, (T*)b.s2, tp, replay, m);
+              else
+                k_steps_1d<T, PHYS, NT2, MODE><<<1, NT2, 0, s>>>(a, k, (T*)b.s1, (T*)b.s2, tp, replay, m);
+            };
+            if (may_time)
+              timed(s, steps);
             else
-              k_steps_1d<T, PHYS, NT2, MODE><<<1, NT2, 0, s>>>(a, k, (T*)b.s1, (T*)b.s2, tp, replay, m);
+              steps();
           };
           if constexpr (PHYS == PH_EULER)
             with_mode(p, launch);

@@ -382,7 +382,8 @@ class Stepper:
 
 
 def timing_begin(enable: bool = True):
-    """Start timing every Runge-Kutta stage-kernel launch (HIP events on its stream)."""
+    """Start timing every Runge-Kutta stage-kernel launch (HIP events on its stream); small
+    1D grids, whose steps share a launch, are timed by that launch."""
     _check(lib().hweno_timing_begin(1 if enable else 0), "hweno_timing_begin")
 
 
