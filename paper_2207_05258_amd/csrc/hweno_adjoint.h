@@ -82,7 +82,7 @@ HW_HD T hw_blend_vjp(T A, T B, T H0, T Hs, T Hd, T g1, T g2, T eps, T g, T& gA, 
   return r;
 }
 
-// reverse of hw_plus() (accumulates); returns the forward value
+// reverse of hw_plus() (accumulates; for checks, as it is); returns the forward value
 template <typename T>
 HW_HD T hw_plus_vjp(T fm, T f0, T fp, T Hm, T H0, T Hp, const Weights<T>& w, T g, T& gfm,
                     T& gf0, T& gfp, T& gHm, T& gH0, T& gHp) {
@@ -125,7 +125,8 @@ HW_HD T limit_blend_vjp(T d1, T d2, T Vs, T Vd, T g1, T g2, T eps, T g, T& gd1, 
   return r;
 }
 
-// reverse of limit1() (accumulates)
+// reverse of limit1() (accumulates): limit_blend_vjp around the scheme's own arguments,
+// for checks
 template <typename T>
 HW_HD void limit1_vjp(T um, T u0, T up, T vm, T vp, T h, T ih, const Weights<T>& w, T g,
                       T& gum, T& gu0, T& gup, T& gvm, T& gvp) {
@@ -224,7 +225,7 @@ HW_HD void point_fluxes_vjp(const T* U, const T* Dn, const T* Dt, const Consts<T
 // adjoints of the Roe eigen-system quantities used by project() / back()
 template <typename T>
 struct EigenAdj {
-  T un = 0, ut = 0, H = 0, c = 0, ic = 0, b1 = 0, b2 = 0, hq2 = 0;
+  T un = 0, ut = 0, H = 0, c = 0, ic = 0, b1 = 0, hq2 = 0;
 };
 
 // reverse of Eigen::project(): gx = L^T gw, plus eigen-system adjoints
@@ -310,12 +311,9 @@ HW_HD void roe_vjp(const T* UL, const T* UR, T gm1, const EigenAdj<T>& g, T* gUL
   const T hq2 = T(0.5) * (un * un + ut * ut);
   const T c2 = gm1 * (H - hq2);
   const T ic = fast_rsq(c2);
-  const T c = c2 * ic;
-  const T b1 = gm1 * ic * ic;
-  // b2 = b1 hq2, b1 = gm1 ic^2, ic = 1/c, c = sqrt(gm1 (H - hq2))
-  const T gb1 = g.b1 + hq2 * g.b2;
-  T ghq2 = g.hq2 + b1 * g.b2;
-  const T gic = g.ic + T(2) * gm1 * ic * gb1;
+  // b1 = gm1 ic^2, ic = 1/c, c = sqrt(gm1 (H - hq2))
+  T ghq2 = g.hq2;
+  const T gic = g.ic + T(2) * gm1 * ic * g.b1;
   const T gc = g.c - ic * ic * gic;
   const T gcc = gm1 * T(0.5) * ic * gc;
   const T gH = g.H + gcc;
@@ -380,7 +378,7 @@ HW_HD void limit_char_d_vjp(const T* u0, const T* d1, const T* d2, const T* Vs, 
   roe_vjp<T, M>(u0, u0, gm1, ge, gu0, gu0);
 }
 
-// reverse of limit_char() (accumulates into gum, gu0, gup, gvm, gvp)
+// reverse of limit_char(), likewise (accumulates into gum, gu0, gup, gvm, gvp)
 template <typename T, int M>
 HW_HD void limit_char_vjp(const T* um, const T* u0, const T* up, const T* vm, const T* vp, T h,
                           T ih, const Weights<T>& w, T gm1, const T* gout, T* gum, T* gu0,

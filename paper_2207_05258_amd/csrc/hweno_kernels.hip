@@ -837,13 +837,13 @@ __device__ __forceinline__ void stage_tile(const StageArgs<T>& a, const Consts<T
 // four steps of 2047 x 1531, and 5.09 against 5.65 ms for a step of 256
 // batched grids walked by resident workgroups, whose kernel spills most.  FP64: two
 // (220-224 VGPRs, no spills); a third would need 168 and spills 352 B.
-template <typename T, int K>
+template <typename T>
 struct StageOcc {
   static constexpr int WAVES = sizeof(T) == 4 ? 4 : 2;
 };
 
 template <typename T, int PHYS, int DIM, int K, int TX, int TY, int NT, int MODE>
-__global__ __launch_bounds__(NT, (StageOcc<T, K>::WAVES)) void k_stage(StageArgs<T> a, Consts<T> k) {
+__global__ __launch_bounds__(NT, StageOcc<T>::WAVES) void k_stage(StageArgs<T> a, Consts<T> k) {
   constexpr int M = Comps<PHYS, DIM>::M;
   constexpr int NF = Comps<PHYS, DIM>::NF;
   constexpr int HY = (DIM == 2) ? 2 : 0;
@@ -874,14 +874,9 @@ __global__ __launch_bounds__(NT, (StageOcc<T, K>::WAVES)) void k_stage(StageArgs
 // 2D Euler with edge-described sides.  The body
 // repeats k_stage's: handing the kernel parameters to a shared device
 // function by reference costs k_stage its register allocation (spills).
-// Three waves per SIMD in FP32: at five the boundary fix-up spills.
-template <typename T>
-struct EdgeOcc {
-  static constexpr int WAVES = sizeof(T) == 4 ? 3 : 2;
-};
-
+// (FP32 126-128 VGPRs, FP64 up to 226, without spills.)
 template <typename T, int K, int TX, int TY, int NT, int MODE>
-__global__ __launch_bounds__(NT, (EdgeOcc<T>::WAVES)) void k_stage_edges(StageArgs<T> a,
+__global__ __launch_bounds__(NT, StageOcc<T>::WAVES) void k_stage_edges(StageArgs<T> a,
                                                                              Consts<T> k,
                                                                              EdgeArgs e) {
   constexpr int PHYS = PH_EULER, DIM = 2;
@@ -988,7 +983,7 @@ __device__ __forceinline__ void batched_tile(const hweno_instance* __restrict__ 
 // atomics on the same control line.  Otherwise: persistent, striding over
 // XCD bands of the tile list.
 template <typename T, int V, int K, bool ONE, int MODE>
-__global__ __launch_bounds__(256, (StageOcc<T, K>::WAVES)) void k_stage_batched(
+__global__ __launch_bounds__(256, StageOcc<T>::WAVES) void k_stage_batched(
     const hweno_instance* __restrict__ inst, const int* __restrict__ tile_map, int total,
     double cfl, Consts<T> k) {
   constexpr int TX = BatchTile<V>::TX, TY = BatchTile<V>::TY;
@@ -2240,7 +2235,6 @@ Consts<T> make_consts(const hweno_problem* p) {
   k.gam = T(p->gamma_gas);
   k.ax = T(p->adv_speed[0]);
   k.ay = T(p->adv_speed[1]);
-  k.characteristic = p->characteristic ? 1 : 0;
   k.limiter_on = p->limiter_on ? 1 : 0;
   k.limiter_char = p->limiter_characteristic ? 1 : 0;
   k.rb = recon_blend(T(p->lin_w[1]), T(p->lin_w[2]), T(p->eps));

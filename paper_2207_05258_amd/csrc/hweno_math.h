@@ -33,7 +33,7 @@ template <typename T>
 struct Weights {
   T g0, g1, g2;  // linear weights, positive, summing to one
   T eps;         // epsilon of the nonlinear weights
-  T gs;          // g0 + g1 + g2
+  T gs;          // g0 + g1 + g2: one, so no formula below reads it
 };
 
 // a b + c, rounded once
@@ -54,20 +54,18 @@ struct Consts {
   T gm1;          // gamma_gas - 1
   T gam;          // gamma_gas
   T ax, ay;       // advection speeds (linear advection)
-  int characteristic;
   int limiter_on;
   int limiter_char;  // Euler: limiter on characteristic fields of each cell
   Blend<T> rb;    // rw and lw in the kernels' units (recon_blend, limit_blend)
   Blend<T> lb;
 };
 
-// Reciprocal, quotient and reciprocal square root of finite, positive,
-// normal arguments (densities, squared sound speeds, sums of positive
-// weights) without the IEEE special-case scaling of the library routines.
+// Reciprocal and reciprocal square root of finite, positive, normal
+// arguments (densities, squared sound speeds, indicators) without the IEEE
+// special-case scaling of the library routines.
 // FP32: the hardware instructions (1 ulp).  FP64: the hardware approximation
 // (relative error about 2^-24 on gfx950, measured) refined by one Newton step,
-// which leaves about 2^-48; a quotient gets one residual correction on top
-// (about 1 ulp).  The host build of the math (CPU unit checks) divides.
+// which leaves about 2^-48.  The host build of the math (CPU unit checks) divides.
 template <typename T>
 HW_HD T fast_rcp(T x);
 template <>
@@ -85,18 +83,6 @@ HW_HD double fast_rcp<double>(double x) {
   return mad(r, mad(-x, r, 1.0), r);
 #else
   return 1.0 / x;
-#endif
-}
-
-template <typename T>
-HW_HD T fast_div(T n, T d) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  const T r = fast_rcp(d);
-  const T q = n * r;
-  if constexpr (sizeof(T) == 8) return mad(mad(-d, q, n), r, q);
-  return q;
-#else
-  return n / d;
 #endif
 }
 
@@ -121,9 +107,10 @@ HW_HD double fast_rsq<double>(double x) {
 #endif
 }
 
-// quotient n / d of a finite n and a positive normal d whose result is a
-// correction added to a larger term: the reciprocal's error e is expanded to
-// second order, q (1 + e + e^2), instead of refining the reciprocal first
+// Quotient n / d of a finite n and a positive normal d, without that scaling
+// either.  FP64: the error e of the hardware reciprocal (about 2^-24) is expanded to
+// second order, q (1 + e + e^2), which leaves 2^-72 and the roundings of q and of the
+// result, about 1 ulp.
 template <typename T>
 HW_HD T blend_div(T n, T d) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -237,7 +224,8 @@ HW_HD T hw_blend(T A, T B, T H0, T Hs, T Hd, const Blend<T>& w) {
                      [=](T m, T s1, T s2, T f) { return mad(m, R0, f * mad(s1, u1, -(s2 * u2))); });
 }
 
-// the whole value (single data)
+// the whole value (single data): hw_blend as the scheme's formula is written, for
+// checks against it
 template <typename T>
 HW_HD T hw_plus(T fm, T f0, T fp, T Hm, T H0, T Hp, const Weights<T>& w) {
   const T r = hw_blend(T(2) * (fm - f0), T(2) * (fp - f0), T(2) * H0, T(2) * (Hm + Hp),
@@ -327,7 +315,7 @@ HW_HD void point_fluxes(const T* U, const T* Dn, const T* Dt,
 // (1D drops ut), left eigenvectors = their inverse in closed form.
 template <typename T, int M>
 struct Eigen {
-  T un, ut, H, c, ic, b1, b2, hq2;
+  T un, ut, H, c, ic, b1, hq2;
 
   HW_HD void roe(const T* UL, const T* UR, T gm1) {
     // sqrt(rho) and 1/rho from one reciprocal square root per side
@@ -350,7 +338,6 @@ struct Eigen {
     ic = fast_rsq(c2);
     c = c2 * ic;
     b1 = gm1 * ic * ic;
-    b2 = b1 * hq2;
   }
 
   // eigen-system at one state (what the Roe average of a state with itself gives)
@@ -365,7 +352,6 @@ struct Eigen {
     ic = fast_rsq(c2);
     c = c2 * ic;
     b1 = gm1 * ic * ic;
-    b2 = b1 * hq2;
   }
 
   // w = L x
