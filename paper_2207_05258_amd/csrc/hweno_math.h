@@ -179,11 +179,14 @@ HW_HD T blend_c(T c0, T c1, T c2, const Blend<T>& w, const Num& num) {
 }
 
 // Reconstruction weights for hw_blend, whose data are twice the split fluxes
-// and whose indicators carry 12/13: kappa = 13/48, eps 12/13.
+// and whose indicators carry 12/13: kappa = 13/48, eps 12/13 (FP32: kept normal, as
+// the hardware reciprocal takes a denormal for zero).
 template <typename T>
 HW_HD Blend<T> recon_blend(T g1, T g2, T eps) {
   const T kap = sizeof(T) == 8 ? T(13.0 / 48.0) : T(1);
-  return Blend<T>{kap * g1, kap * g2, T(12.0 / 13.0) * eps};
+  T e = T(12.0 / 13.0) * eps;
+  if constexpr (sizeof(T) == 4) e = e < T(1.17549435e-38) ? T(1.17549435e-38) : e;
+  return Blend<T>{kap * g1, kap * g2, e};
 }
 // limiter weights for limit_blend: kappa = 1/4
 template <typename T>

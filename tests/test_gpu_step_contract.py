@@ -148,3 +148,19 @@ def test_batched_workspaces_hold_no_partial_speeds():
     for q, w in enumerate(ws):
         prob = h.Problem(dim=2, nx=w.nx, ny=w.ny, physics="euler", dtype=torch.float64, dx=w.dx, dy=w.dy)
         assert int(b._host[q].ws_bytes) == h.workspace_bytes(prob) - 1024
+
+
+# ---- the smallest normal epsilon of each type ----
+@pytest.mark.parametrize("dim", [1, 2])
+def test_smallest_normal_epsilon_in_fp32(dim):
+    """A constant state has no rate of change with any positive epsilon: all indicators are
+    epsilon, whose reciprocal is finite down to the smallest normal number."""
+    m = dim + 2
+    S = torch.zeros(m * (1 + dim), 33 if dim == 2 else 1, 40, device="cuda")
+    S[0], S[1], S[m - 1] = 1.0, 0.5, 2.5
+    prob = h.Problem(dim=dim, nx=40, ny=S.shape[1], physics="euler", dtype=torch.float32, dx=0.1, dy=0.1,
+                     eps=float(torch.finfo(torch.float32).tiny))
+    X = S.clone()
+    assert torch.equal(h.rhs(S, prob), torch.zeros_like(S))
+    h.Stepper(prob).step(X)
+    assert torch.isfinite(X).all() and float((X - S).abs().max()) <= 1e-6
