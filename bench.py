@@ -54,23 +54,23 @@ FIELDS_PER_CELL_STAGE_SCOPE = 32.0
 # reports null).
 MEASURED_TRAFFIC = {
     # profiles/k_stage_euler2d_4096_f64_hbm_bytes.md, profiles/k_stage_euler2d_4096_f32_hbm_bytes.md
-    ("262bcc26cfe90da7", "f64", 4096): 5.0817e+09,
-    ("262bcc26cfe90da7", "f32", 4096): 2.5437e+09,
+    ("970b5280f97c66d7", "f64", 4096): 5.0811e+09,
+    ("970b5280f97c66d7", "f32", 4096): 2.5440e+09,
 }
 
 # VALU wave-instructions issued by one stage-kernel launch (rocprofv3 --pmc
 # SQ_INSTS_VALU, average of the three stages), keyed like MEASURED_TRAFFIC.
 MEASURED_VALU_WAVE_INSTR = {
     # profiles/k_stage_euler2d_4096_sq_counters.md
-    ("262bcc26cfe90da7", "f64", 4096): 7.124e8,
-    ("262bcc26cfe90da7", "f32", 4096): 6.871e8,
+    ("970b5280f97c66d7", "f64", 4096): 7.134e8,
+    ("970b5280f97c66d7", "f32", 4096): 6.881e8,
 }
 # Floating-point operations per FP64 cell-stage that the SQ counters of the same
 # device code count (SQ_INSTS_VALU_{ADD,MUL,TRANS}_F64 + 2 x FMA over cells x
 # stages), keyed like MEASURED_TRAFFIC.
 MEASURED_FLOP_PER_CELL_STAGE = {
     # profiles/k_stage_euler2d_4096_sq_counters.md
-    ("262bcc26cfe90da7", "f64", 4096): 3424.0,
+    ("970b5280f97c66d7", "f64", 4096): 3424.0,
 }
 # VALU issue peak of the chip in lane-instructions/s: 256 CUs x 4 SIMDs x 2.4 GHz
 # x 16 lanes per cycle for FP64, x 32 for FP32 (the FP32 vector peak of 157.3
@@ -84,7 +84,7 @@ PEAK_VALU_LANE_INSTR = {"f64": 256 * 4 * 16 * 2.4e9, "f32": 256 * 4 * 32 * 2.4e9
 # keyed by the hash of the k_adjoint kernels' machine code
 ADJOINT_PREFIX = "_ZN5hweno9k_adjointI"
 MEASURED_ADJOINT = {
-    ("ac60f58eaa432ba3", "f32", 512): {"flop": 3.356e7 * 64, "valu_wave_instr": 3.040e7},
+    ("952ee14d24ad8ccd", "f32", 512): {"flop": 3.349e7 * 64, "valu_wave_instr": 3.035e7},
 }
 
 

@@ -1694,13 +1694,13 @@ __global__ __launch_bounds__(64) void k_finish(double* ctrl, double* fold, int s
 // n_steps whole steps of a 1D grid that one workgroup holds (nx < NT: one thread
 // per cell and per interface).  The state stays in registers and LDS; each step
 // does what k_begin, k_alpha, the three stages and k_finish do, with the same
-// functions and in the same order, and leaves the same control block, tapes and
-// stage states behind.
+// formulas in the same order, and leaves the same control block, tapes and
+// stage states behind (up to the last bits: the compiler fuses other operations).
 // A stage of such a grid is a few hundred instructions, and a step by launches was
 // nothing but their cost: 64 steps of 200 cells of linear advection took 256
-// launches at 3.6 us each, 0.93 ms, and take 0.25 ms in one.  Two barriers per stage order the two state buffers,
-// the fluxes and the speeds: whoever writes one of them has passed a barrier
-// after its last reads.
+// launches at 3.6 us each, 0.93 ms, and take 0.25 ms in one.  Two barriers per stage
+// order the two state buffers, the fluxes and the speeds: whoever writes one of them
+// has passed a barrier after its last reads.
 // ---------------------------------------------------------------------------
 template <typename T, int PHYS, int NT, int MODE>
 __global__ __launch_bounds__(NT) void k_steps_1d(StageArgs<T> a, Consts<T> k, T* s1, T* s2,
@@ -1915,8 +1915,10 @@ struct LimNb {
 // columns of 256 / 2^lx rows, so that no thread divides to find its cell.  EDG:
 // edge-described sides and obstacles; they index the kernel's arguments by lane, which
 // the compiler serves from a copy in scratch memory (424 B a thread), and so are an
-// instantiation of their own.  2D Euler, 1024^2: FP64 138 -> 27 us (6.2 TB/s of one read
-// and one write), FP32 114 -> 19 us; 1999 x 1501 FP64 389 -> 130 us.
+// instantiation of their own, which is as slow as every grid was before.  2D Euler
+// without them, 1999 x 1501 FP64: 389 -> 130 us, 3.7 TB/s of one read and one write (a
+// large copy reaches 5.1); 1024^2, whose 168 MB (FP64) partly stay in the last-level
+// cache from call to call: FP64 138 -> 27 us, FP32 114 -> 19 us.
 template <typename T, int PHYS, int DIM, bool EDG>
 __global__ __launch_bounds__(256) void k_limit(const T* __restrict__ S, T* __restrict__ out,
                                                int nx, int ny, int lx, int bc_x, int bc_y,

@@ -439,8 +439,8 @@ HW_HD void limit_char(const T* um, const T* u0, const T* up, const T* vm, const 
 // The stage kernels are bound by VALU issue, so the form is the one with the
 // fewest instructions: with the point data themselves projected, the scheme's
 // factors applied where they occur and the linear fluxes summed point by point, a
-// 2D Euler stage took 3368 VALU instructions per lane (2813 of them FP64), in this
-// form 2722 (2153); two steps of 4096^2 in FP64 went from 13.05 to 11.45 ms, four
+// 2D Euler stage counted 3414 VALU lane-instructions per cell in FP64, in this
+// form 2721; two steps of 4096^2 in FP64 went from 13.05 to 11.45 ms, four
 // of 2047 x 1531 in FP32 from 2.79 to 2.57 ms.
 //   alpha: global LF speed of this direction.
 // ---------------------------------------------------------------------------
