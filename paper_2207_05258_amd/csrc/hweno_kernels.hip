@@ -1235,7 +1235,9 @@ struct AdjOcc {
 // the sums through the point fluxes once per direction, instead of every
 // interface and side doing so for each of its points.  The linear fluxes'
 // adjoints are stencils of the incoming one: each lane leaves its interface's in
-// LDS and the owners apply the four coefficients.
+// LDS and the owners apply the four coefficients.  These pass the point fluxes
+// by themselves, with the mixed flux's: within the sums, 15 times their size would
+// have to cancel again in alpha U's share, whose rounding stays.
 // The additions go point by point: in one phase all lanes add to stencil point s of
 // their interfaces, which are distinct cells, and a barrier ends the phase.  So
 // the sums need no atomics and have a fixed order.  The barriers also keep
@@ -1365,11 +1367,10 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
 #pragma unroll
       for (int c = 0; c < M; ++c) acc[cs(c) * AS] += gU[c], acc[(ON + cs(c)) * AS] += gN[c];
     };
-    T lF[M], lA[M];
     if (owner) {
       // linear fluxes: the cell is point s of interface q0 + (3 - s) CS
       const int q0 = d == 0 ? ly * (TX + 3) + lx : ly * TX + lx;
-      T gU[M], gN[M], gT[M], gB[M];
+      T lF[M], lA[M], gU[M], gN[M], gT[M], gB[M];
       bool some = false, mixed = false;
 #pragma unroll
       for (int c = 0; c < M; ++c) {
@@ -1377,10 +1378,8 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
         const T p3 = g[0], p2 = g[CS], p1 = g[2 * CS], p0 = g[3 * CS];
         lF[c] = mad(T(15), p2 - p1, p0 - p3);
         lA[c] = T(1.0 / 3.0) * mad(T(-7), p1 + p2, p0 + p3);
-        // U and Dn themselves, less what the sums of x+ and y+, which start from
-        // lF and lA, will add
-        gU[c] = alpha * ((p0 + p3) - (p1 + p2) - lF[c]);
-        gN[c] = alpha * mad(T(1.0 / 3.0), mad(T(3), p1 - p2, p0 - p3), -lA[c]);
+        gU[c] = alpha * ((p0 + p3) - (p1 + p2));
+        gN[c] = (T(1.0 / 3.0) * alpha) * mad(T(3), p1 - p2, p0 - p3);
         some = some || p0 != T(0) || p1 != T(0) || p2 != T(0) || p3 != T(0);
         gT[c] = T(0);
         if constexpr (DIM == 2) {
@@ -1389,22 +1388,27 @@ __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, 
           mixed = mixed || gB[c] != T(0);
         }
       }
-      if (some) add_cell(gU, gN);
-      if constexpr (DIM == 2) {
-        if (mixed) {
-          T U[M], Dt[M];
+      if (some || mixed) {
+        // fields that meet zero adjoints only stay out (they may not be finite)
+        T U[M], Dn[M], Dt[M];
+        ld(own, U, Dn);
 #pragma unroll
-          for (int c = 0; c < M; ++c) U[c] = own[cs(c)], Dt[c] = own[OT + cs(c)], gU[c] = T(0);
-          point_fluxes_vjp<T, PHYS, M, true, false>(U, Dt, Dt, k, an, nullptr, nullptr, gB, gU, gT, gT);
+        for (int c = 0; c < M; ++c) {
+          Dn[c] = some ? Dn[c] : T(0);
+          Dt[c] = DIM == 2 && mixed ? own[OT + cs(c)] : T(0);
+        }
+        point_fluxes_vjp<T, PHYS, M, DIM == 2>(U, Dn, Dt, k, an, lF, lA, gB, gU, gN, gT);
+        add_cell(gU, gN);
+        if constexpr (DIM == 2) {
 #pragma unroll
-          for (int c = 0; c < M; ++c) acc[cs(c) * AS] += gU[c], acc[(OT + cs(c)) * AS] += gT[c];
+          for (int c = 0; c < M; ++c) acc[(OT + cs(c)) * AS] += gT[c];
         }
       }
     }
     __syncthreads();
     if (owner) {
 #pragma unroll
-      for (int c = 0; c < M; ++c) pool[c * AS + tid] = lF[c], pool[(M + c) * AS + tid] = lA[c];
+      for (int c = 0; c < 2 * M; ++c) pool[c * AS + tid] = T(0);
     }
     // ---- the nonlinear flux, "+" side then "-" side ----
     const T* base = cell(i1 - (d == 0 ? 1 : 0), j1 - (d == 1 ? 1 : 0));
