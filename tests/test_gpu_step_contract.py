@@ -164,3 +164,19 @@ def test_smallest_normal_epsilon_in_fp32(dim):
     assert torch.equal(h.rhs(S, prob), torch.zeros_like(S))
     h.Stepper(prob).step(X)
     assert torch.isfinite(X).all() and float((X - S).abs().max()) <= 1e-6
+
+
+# ---- FP32: a step whose operator is zero leaves the conserved fields as they are ----
+@pytest.mark.parametrize("dim,n", [(1, 300), (1, 1500), (2, 40)])
+def test_fp32_step_without_rates_keeps_every_bit(dim, n):
+    """Linear advection at rest: no flux, no splitting speed, so each stage combines a value
+    with itself, which the difference form returns exactly (3/4 and 1/3 of it rounded first
+    do not)."""
+    g = torch.Generator().manual_seed(2)
+    ny = 33 if dim == 2 else 1
+    S = (torch.rand(1 + dim, ny, n, generator=g) + 0.5).cuda()
+    prob = h.Problem(dim=dim, nx=n, ny=ny, physics="linadv", dtype=torch.float32, dx=0.1, dy=0.1,
+                     adv_speed=(0.0, 0.0))
+    X = S.clone()
+    h.Stepper(prob).steps(X, 4, dt=0.05)
+    assert torch.equal(X[0], S[0]) and torch.isfinite(X).all()
