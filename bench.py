@@ -54,23 +54,23 @@ FIELDS_PER_CELL_STAGE_SCOPE = 32.0
 # reports null).
 MEASURED_TRAFFIC = {
     # profiles/k_stage_euler2d_4096_f64_hbm_bytes.md, profiles/k_stage_euler2d_4096_f32_hbm_bytes.md
-    ("970b5280f97c66d7", "f64", 4096): 5.0811e+09,
-    ("970b5280f97c66d7", "f32", 4096): 2.5440e+09,
+    ("8bab44da3a0e5b56", "f64", 4096): 5.0817e+09,
+    ("8bab44da3a0e5b56", "f32", 4096): 2.5431e+09,
 }
 
 # VALU wave-instructions issued by one stage-kernel launch (rocprofv3 --pmc
 # SQ_INSTS_VALU, average of the three stages), keyed like MEASURED_TRAFFIC.
 MEASURED_VALU_WAVE_INSTR = {
     # profiles/k_stage_euler2d_4096_sq_counters.md
-    ("970b5280f97c66d7", "f64", 4096): 7.134e8,
-    ("970b5280f97c66d7", "f32", 4096): 6.881e8,
+    ("8bab44da3a0e5b56", "f64", 4096): 7.134e8,
+    ("8bab44da3a0e5b56", "f32", 4096): 6.881e8,
 }
 # Floating-point operations per FP64 cell-stage that the SQ counters of the same
 # device code count (SQ_INSTS_VALU_{ADD,MUL,TRANS}_F64 + 2 x FMA over cells x
 # stages), keyed like MEASURED_TRAFFIC.
 MEASURED_FLOP_PER_CELL_STAGE = {
     # profiles/k_stage_euler2d_4096_sq_counters.md
-    ("970b5280f97c66d7", "f64", 4096): 3424.0,
+    ("8bab44da3a0e5b56", "f64", 4096): 3424.0,
 }
 # VALU issue peak of the chip in lane-instructions/s: 256 CUs x 4 SIMDs x 2.4 GHz
 # x 16 lanes per cycle for FP64, x 32 for FP32 (the FP32 vector peak of 157.3
