@@ -1262,7 +1262,7 @@ struct AdjOcc {
 // Measured (one launch under the profiler): with every interface reversing the point
 // fluxes of its six point data itself and handing 12 fields over per point, 512^2
 // FP32 took 116 us (9278 VALU instructions per lane) and 128^2 FP64 47 us; in this
-// form 79 us (6100) and 35 us.
+// form 77 us (5950) and 35 us.
 template <typename T, int PHYS, int DIM, int TX, int TY, int NT, int MODE>
 __global__ __launch_bounds__(NT, AdjOcc<T>::WAVES) void k_adjoint(AdjArgs<T> a, Consts<T> k) {
   constexpr int M = Comps<PHYS, DIM>::M;
